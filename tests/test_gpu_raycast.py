@@ -122,3 +122,67 @@ def test_virtual_depth_helper_refines_holes(rf):
         errs.append(np.abs(z[sel] - truth[sel]))
         assert (z[seq.depth[k] == 0] > 0).all()                    # no zero is left
     assert np.median(np.concatenate(errs)) < 0.01
+
+
+@pytest.mark.parametrize("storage,orc_storage", [("fp32", 0), ("fp16", 1)])
+@pytest.mark.parametrize("W,H,holes,s,tau", [
+    (1, 1, 1.0, 0.01, 0.05), (17, 15, 1.0, 0.01, 0.05), (47, 33, 0.05, 0.01, 0.05), (47, 33, 0.16, 0.01, 0.05),
+    (64, 48, 0.5, 0.01, 0.05), (64, 48, 1.0, 0.02, 0.01), (33, 31, 1.0, 0.02, 0.4), (40, 40, 1.0, 0.006, 0.02),
+])
+def test_raycast_paths_match_the_mirror(rf, W, H, holes, s, tau, storage, orc_storage):
+    """Few and many rays a tile, ragged tiles, samples shorter than a voxel
+    and longer than a block, more blocks than the tile's table holds, rays
+    through blocks that are absent, partly observed, free and mixed, and a
+    pose far off the origin: bit-exact against the FP32 mirror."""
+    rng = np.random.default_rng(7)
+    far = 0.0 if holes < 1.0 else 40.0
+    c, r = np.array([0.05 + far, -0.03, 1.0]), 0.25
+    B = 8 * s
+    lo = np.floor((c - [0.9, 0.7, 0.9]) / B).astype(int)
+    hi = np.ceil((c + [0.9, 0.7, 0.6]) / B).astype(int)
+    keys = np.array([[x, y, z] for x in range(lo[0], hi[0]) for y in range(lo[1], hi[1]) for z in range(lo[2], hi[2])],
+                    np.int32)
+    keys = keys[rng.uniform(size=len(keys)) > 0.03]               # some blocks are absent
+    keys = keys[rng.permutation(len(keys))[:30000]]
+    k, sdf, w, rgb = A.fill_map(keys, s, lambda x: np.clip(np.minimum(np.linalg.norm(x - c, axis=-1) - r,
+                                                                     1.45 - x[..., 2]), -tau, tau))
+    w = np.where(rng.uniform(size=w.shape) < 2e-5, 0.0, w)         # and a few voxels unobserved
+    mp = rf.MapParams(s, tau, 5.0, 1 << 17, 1 << 15, 255, 4, storage, 64 * 64)
+    m = rf.Map(mp)
+    sdf32 = sdf.astype(np.float32)
+    m.import_(torch.from_numpy(k).cuda(), torch.from_numpy(sdf32).cuda(),
+              torch.from_numpy(w.astype(np.float32)).cuda(), torch.from_numpy(rgb).cuda())
+    o32 = O.OracleMap(s, tau, 5.0, 255, 4, real_bits=32, storage=orc_storage)
+    # the mirror imports values as they are, so it gets what the map holds (16-bit storage rounds)
+    ke, se, we, ce = [t.cpu().numpy() for t in m.export()]
+    o32.import_(ke, se.astype(np.float64), we.astype(np.float64), ce)
+    depth = np.where(rng.uniform(size=(H, W)) < holes, 0.0, 1.5).astype(np.float32)
+    g, o = frames_for(rf, W, H, 0.8 * max(W, 16), depth)
+    T = np.eye(4)
+    T[:3, :3] = [[0.96, 0.0, 0.28], [0.0, 1.0, 0.0], [-0.28, 0.0, 0.96]]
+    T[:3, 3] = [far - 0.25, 0.02, 0.03]
+    for only in ([True, False] if holes < 1.0 else [False]):
+        zg = m.raycast(g, dev_pose(T), z_near=0.1, z_far=2.0, far_value=4.0, only_invalid=only).cpu().numpy()
+        z32 = o32.raycast(o, T, z_near=0.1, z_far=2.0, far_value=4.0, only_invalid=only)
+        assert W == 1 or tau < 0.02 or (zg > 0).mean() > 0.2
+        assert np.array_equal(zg, z32)
+
+
+def test_raycast_through_free_blocks_matches_the_mirror(rf):
+    """Compact free space: rays step over free blocks and blocks with voxels."""
+    seq = synth.parity_room(n_frames=4)
+    mp = map_params(rf, seq)
+    mp.free_blocks = True
+    m = rf.Map(mp)
+    o32 = O.OracleMap(seq.voxel_size, seq.truncation, seq.depth_max, 255, seq.carve_stride, real_bits=32,
+                      free_blocks=True)
+    for k in range(3):
+        g, P = gpu_frame(rf, seq, k), dev_pose(seq.poses[k])
+        m.allocate(g, P)
+        m.integrate(g, P)
+        o32.allocate(orc_frame(seq, k), seq.poses[k])
+        o32.integrate(orc_frame(seq, k), seq.poses[k])
+    zg = m.raycast(gpu_frame(rf, seq, 3), dev_pose(seq.poses[3]), only_invalid=False).cpu().numpy()
+    z32 = o32.raycast(orc_frame(seq, 3), seq.poses[3], z_far=seq.depth_max, only_invalid=False)
+    assert (zg > 0).mean() > 0.5
+    assert np.array_equal(zg, z32)
