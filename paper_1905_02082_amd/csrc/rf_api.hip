@@ -182,12 +182,15 @@ rf_status mask_checks(const rf_job& j, rf::Job& J) {
 }
 
 // ------------------------------------------- allocation-free mask variant
-// compute_dynamic_mask_static keeps the flood fill's per-pixel mask and its
-// two buffers of tile flags in this file-scope device array instead of the
-// map arena.  Each GPU holds its own copy at its own address until the
-// process ends; host code uses only the address hipGetSymbolAddress returns
-// for the current device, never the array's name.
-constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
+// compute_dynamic_mask_static keeps the flood fill's bits and its two buffers
+// of tile flags in this file-scope device array instead of the map arena.
+// Each GPU holds its own copy at its own address until the process ends; host
+// code uses only the address hipGetSymbolAddress returns for the current
+// device, never the array's name.
+// A frame of the largest accepted size needs 9 bits a pixel, its lines padded
+// to 64 pixels (lines of at least 256, or the longer side), and its tile flags.
+constexpr size_t kStaticFrameBytes = (size_t)4 << 20;
+constexpr size_t kStaticScratchBytes = (size_t)6 << 20;
 __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -369,7 +372,7 @@ rf_status compute_dynamic_mask_stages(rf_map* m, const rf_frame* f, const double
     J.residual = d_residual_out;
     return RF_OK;
   };
-  auto launch = [&](rf::Batch& b, int df, int sto) { rf::launch_mask(b, df, sto, *mp, S(stream)); };
+  auto launch = [&](rf::Batch& b, int df, int sto) { rf::launch_mask(b, df, sto, *mp, nullptr, S(stream)); };
   return run_batches(&j, 1, "compute_dynamic_mask", fill, launch);
 }
 
@@ -385,14 +388,17 @@ rf_status compute_dynamic_mask_static(rf_map* m, const rf_frame* f, const double
   rf::FrameDev fd;
   rf_status st = make_frame(f, fd);
   if (st) return st;
-  // the flood fill's scratch: the per-pixel mask, then two buffers of tile flags
+  // the flood fill's scratch: the members, two buffers of tile flags, the rule's bits
   const size_t npx = (size_t)fd.W * (size_t)fd.H;
   const uint32_t tiles = (uint32_t)((fd.W + rf::kTile - 1) / rf::kTile) * (uint32_t)((fd.H + rf::kTile - 1) / rf::kTile);
-  const size_t flags_at = align256(npx);
-  const size_t need = flags_at + (size_t)2 * tiles * 4;
-  if (need > kStaticScratchBytes)
-    return fail(RF_ENOMEM, "compute_dynamic_mask_static: a %dx%d frame needs %zu bytes of scratch, the static "
-                "array holds %zu", fd.W, fd.H, need, kStaticScratchBytes);
+  const size_t need = align256(npx) + (size_t)2 * tiles * 4;
+  if (need > kStaticFrameBytes)
+    return fail(RF_ENOMEM, "compute_dynamic_mask_static: a %dx%d frame needs %zu bytes of scratch, the limit is %zu",
+                fd.W, fd.H, need, kStaticFrameBytes);
+  const size_t flags_at = align256(rf::flood_member_bytes(fd));
+  const size_t edges_at = align256(flags_at + (size_t)2 * tiles * 4);
+  if (edges_at + rf::flood_edge_bytes(fd) > kStaticScratchBytes)
+    return fail(RF_ENOMEM, "compute_dynamic_mask_static: a %dx%d frame does not fit the static array", fd.W, fd.H);
   void* base = nullptr;
   st = static_scratch(&base);
   if (st) return st;
@@ -416,7 +422,7 @@ rf_status compute_dynamic_mask_static(rf_map* m, const rf_frame* f, const double
     // the tile flags must start empty; the last call on this device may
     // have used other sizes (a fill kernel, no memset node in a captured graph)
     clear_words_kernel<<<(2 * tiles + 255) / 256, 256, 0, S(stream)>>>(b.job[0].m.dirty, 2 * tiles);
-    rf::launch_mask(b, df, sto, *mp, S(stream));
+    rf::launch_mask(b, df, sto, *mp, sp + edges_at, S(stream));
   };
   return run_batches(&j, 1, "compute_dynamic_mask_static", fill, launch);
 }
@@ -472,7 +478,7 @@ rf_status compute_dynamic_mask_batch(const rf_job* jobs, int32_t n, const rf_mas
   if (!mp) return fail(RF_EINVAL, "mask params are NULL");
   if (!(mp->gamma >= 0.0f) || !(mp->theta >= 0.0f)) return fail(RF_EINVAL, "gamma and theta must be >= 0");
   auto fill = [&](const rf_job& j, rf::Job& J) -> rf_status { return mask_checks(j, J); };
-  auto launch = [&](rf::Batch& b, int df, int sto) { rf::launch_mask(b, df, sto, *mp, S(stream)); };
+  auto launch = [&](rf::Batch& b, int df, int sto) { rf::launch_mask(b, df, sto, *mp, nullptr, S(stream)); };
   return run_batches(jobs, n, "compute_dynamic_mask", fill, launch);
 }
 

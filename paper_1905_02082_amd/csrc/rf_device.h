@@ -9,9 +9,10 @@
 //   sdfw         max_blocks x 512 x  {f32 sdf, f32 weight} (FP32) | {f16 sdf/tau, u8 weight, pad} (FP16)
 //   rgb          max_blocks x 512 x  uchar4 (RGB + pad)
 //   partials     tracking: 3 buffers of 29 fixed-point accumulators (128 B apart) + 2 poses
-//   mask scratch max_pixels bytes + two buffers of per-tile dirty flags for the flood fill
+//   mask scratch max_pixels bytes (the flood fill's members, a bit each) + two buffers of per-tile dirty flags
 //   tile refs    tracking block cache: per level l < kCacheLevels, tc_tiles x tile_refs(l) x 16 B {key, slot, epoch},
-//                then kCacheLevels x tc_tiles x 4 B pair counts
+//                then kCacheLevels x tc_tiles x 4 B pair counts (the end of the last level, which a frame's few
+//                tiles at that level do not reach, holds the flood fill's rule bits during a mask call)
 //   mesh scratch 2 x kMeshScratch x 4 B
 //   cells        compact free space only: per 8x8 pixel cell of the frame, its smallest measured depth
 //   wlist        compact free space only: num_buckets x 4 B, the integration's work list
@@ -54,7 +55,7 @@ constexpr int kAccCopies = RF_ACC_COPIES;    // copies of the tracking accumulat
 constexpr int kTrackScratchWords = 3 * kAccCopies * 29 * 16 + 32 + 2 * 48;
 constexpr int kIntegGroups = 1536;  // integration workgroups per launch (all jobs together)
 constexpr int kNE = 29;                    // 21 H + 6 g + cost + count
-constexpr int kTile = 32;                  // flood-fill tile edge
+constexpr int kTile = 32;                  // edge of the tiles the flood fill's flag buffers have room for (it uses 64x64)
 constexpr int kCell = 8;                   // compact free space: depth-cell edge (pixels)
 
 // Tracking block cache: for every pyramid level below kCacheLevels and every

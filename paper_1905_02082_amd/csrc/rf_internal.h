@@ -30,7 +30,6 @@ struct Job {
   uint8_t* eroded;
   uint8_t* filled;
   float* residual;
-  int tiles_x, tiles_y;     // flood-fill tile grid
   int carve_groups;         // allocation: workgroups of carve rays (before the band rays')
   int carve_w, carve_h;     // allocation: carve-grid size
   int cells_w, cells_h;     // integration of a compact free-space map: 8x8 depth cells of the frame
@@ -66,7 +65,11 @@ void launch_integrate(Batch& b, int depth_format, int storage, hipStream_t s);
 void launch_track(Batch& b, int depth_format, int storage, const rf_track_params& tp, hipStream_t s);
 void launch_normal_equations(Batch& b, int depth_format, int storage, int level, float w_c, double* out29,
                              hipStream_t s);
-void launch_mask(Batch& b, int depth_format, int storage, const rf_mask_params& mp, hipStream_t s);
+// edges: the flood fill's rule bits (flood_edge_bytes, one job), or null for
+// the map's own scratch
+void launch_mask(Batch& b, int depth_format, int storage, const rf_mask_params& mp, void* edges, hipStream_t s);
+size_t flood_edge_bytes(const FrameDev& f);    // 8 bits a pixel, lines padded to words
+size_t flood_member_bytes(const FrameDev& f);  // 1 bit a pixel
 // residual and raw decision of the mask (its first stage), through the tracking tile cache
 void launch_residual(Batch& b, int depth_format, int storage, float gamma, hipStream_t s);
 

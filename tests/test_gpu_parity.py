@@ -4,6 +4,8 @@ Bars: allocated block sets and dynamic masks bit-exact; voxel values
 bit-exact against the FP32 mirror (same FP32 decision and value order) and
 within 1e-5 m of the FP64 reference; poses within 1e-4 m / 1e-5 rad of the
 FP64 reference."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -288,6 +290,95 @@ def test_flood_fill_across_the_whole_frame(rf):
         assert np.array_equal(out[key].cpu().numpy(), ref[key]), key
     assert 0 < ref["eroded"].sum() < 0.05 * W * H and ref["filled"].sum() > 0.9 * W * H
     assert m.status()[0] == 0
+
+
+def _serpentine(W, H, rng):
+    """Depths along a corridor three pixels wide that winds through the frame
+    line by line (between lines without a measurement), rising from 1.9 to
+    2.9 m with steps that mostly pass the flood-fill rule and sometimes pass it
+    in one direction only."""
+    vv, uu = np.mgrid[0:H, 0:W]
+    line, odd = vv // 4, (vv // 4) & 1
+    s = line * W + np.where(odd == 0, uu, W - 1 - uu)
+    d = 1.9 + 1.0 * s / max(float(s.max()), 250.0) + rng.normal(0.0, 0.004, (H, W))
+    wall = (vv % 4 == 3) & ~np.where(odd == 0, uu >= W - 3, uu < 3)
+    return np.where(wall, 0.0, d).astype(np.float32)
+
+
+@pytest.mark.parametrize("W,H,across", [
+    (1, 1, False), (5, 3, False), (64, 64, False), (65, 63, True), (63, 130, False), (70, 300, True), (255, 256, False),
+    (300, 70, True), (257, 129, False), (640, 480, True), (1280, 720, False),
+])
+def test_flood_fill_tiles_match_the_mirror(rf, W, H, across):
+    """Edges of the fill's 64-pixel tiles, tall narrow frames (columns along
+    the bits), paths that cross tile borders over and over, one-way steps, and
+    frames with and without the parallel pass: every mask stage bit-exact
+    against the FP32 mirror, and the static variant's mask the same."""
+    rng = np.random.default_rng(W * 1000 + H)
+    f = 0.9 * max(W, H, 64)
+    intr = (f, f, (W - 1) / 2.0, (H - 1) / 2.0)
+    rgb = np.full((H, W, 3), 128, np.uint8)
+    wall = np.full((H, W), 2.0, np.float32)
+    path = _serpentine(H, W, rng).T.copy() if across else _serpentine(W, H, rng)
+    T = np.eye(4)
+    m = rf.Map(rf.MapParams(0.02, 0.06, 5.0, 1 << 16, 1 << 14, 255, 2, "fp32", W * H))
+    P = dev_pose(T)
+    g0, g1 = rf.Frame.from_numpy(wall, rgb, *intr), rf.Frame.from_numpy(path, rgb, *intr)
+    m.allocate(g0, P)
+    m.integrate(g0, P)
+    o32 = O.OracleMap(0.02, 0.06, 5.0, 255, 2, real_bits=32)
+    o32.allocate(O.Frame(wall, rgb, *intr), T)
+    o32.integrate(O.Frame(wall, rgb, *intr), T)
+    ref = o32.mask(O.Frame(path, rgb, *intr), T, 0.5, 0.007)
+    c = rf.MaskParams(0.5, 0.007).c()
+    for _ in range(2):                                             # the second call finds the first's scratch
+        out = m.dynamic_mask(g1, P, rf.MaskParams(0.5, 0.007), stages=True)
+        for key in ("raw", "eroded", "filled", "final"):
+            assert np.array_equal(out[key].cpu().numpy(), ref[key]), key
+        assert np.array_equal(m.dynamic_mask(g1, P, rf.MaskParams(0.5, 0.007)).cpu().numpy(), ref["final"])
+        static = torch.full((H, W), 7, dtype=torch.uint8, device="cuda")
+        st = rf.lib().compute_dynamic_mask_static(m.h, ctypes.byref(g1.s), ctypes.c_void_p(P.data_ptr()), ctypes.byref(c),
+                                                  ctypes.c_void_p(static.data_ptr()), None, None)
+        assert st == 0
+        assert np.array_equal(static.cpu().numpy(), ref["final"])
+    if W >= 64 and H >= 64:
+        assert ref["filled"].sum() > 2 * ref["eroded"].sum() > 0
+    assert m.status()[0] == 0
+
+
+def test_mask_of_a_thin_frame_leaves_the_tracking_cache_sound(rf):
+    """A frame one line high uses the tracking cache's last level up to the
+    tiles whose pairs the flood fill's scratch takes: registration with four
+    levels after a mask equals registration without one."""
+    W, H = 16384, 1
+    rng = np.random.default_rng(3)
+    u = np.arange(W)
+    depth = (1.5 + 0.1 * np.sin(u / 900.0)).astype(np.float32)[None]
+    rgb = rng.integers(0, 255, (H, W, 3)).astype(np.uint8)
+    intr = (9000.0, 9000.0, (W - 1) / 2.0, 0.0)
+    poses = []
+    for mask in (False, True):
+        m = rf.Map(rf.MapParams(0.02, 0.06, 5.0, 1 << 16, 1 << 13, 255, 2, "fp32", W * H))
+        P = dev_pose(np.eye(4))
+        for dy in (-0.02, 0.0, 0.02):                               # a band of voxels around the line's plane
+            Q = np.eye(4)
+            Q[1, 3] = dy
+            g = rf.Frame.from_numpy(depth, rgb, *intr)
+            m.allocate(g, dev_pose(Q))
+            m.integrate(g, dev_pose(Q))
+        tp = rf.TrackParams(4, 3, min_valid=1)
+        start = np.eye(4)
+        start[0, 3] = 0.003
+        for _ in range(2):
+            T = dev_pose(start)
+            m.track(g, T, tp)
+            if mask:
+                m.dynamic_mask(g, P, rf.MaskParams())
+        poses.append(T.cpu().numpy())
+        out = m.normal_equations(g, dev_pose(start), level=3).cpu().numpy()
+        poses.append(out)
+    assert np.array_equal(poses[0], poses[2]) and np.array_equal(poses[1], poses[3])
+    assert poses[1][28] > 0
 
 
 # ---------------------------------------------------------------- surface / checkpoint
