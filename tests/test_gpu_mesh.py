@@ -103,3 +103,67 @@ def test_mesh_capacity_overflow_and_empty_map(rf):
     part = tris.cpu().numpy()
     assert np.array_equal(part, full[:cap])                      # the first cap triangles, in order
     assert L.extract_mesh(m.h, None, 10, ctypes.c_void_p(cnt.data_ptr()), None) != 0   # NULL triangles, cap > 0
+
+
+@pytest.mark.parametrize("storage,orc_storage", [("fp32", 0), ("fp16", 1)])
+@pytest.mark.parametrize("density,holes,absent", [(0.5, 0.0, 0.0), (0.5, 0.02, 0.3), (0.02, 0.01, 0.6), (1.0, 0.3, 0.0)])
+def test_mesh_of_random_blocks_matches_mirror(rf, density, holes, absent, storage, orc_storage):
+    """Every corner pattern, at every face, edge and corner of a block, with
+    and without the neighbours, unobserved voxels and voxels at the band's
+    limit: the triangles bit-exact against the FP32 mirror, the same again, and
+    the marks of the blocks gone afterwards (the next frame list is right)."""
+    rng = np.random.default_rng(11)
+    s, tau = 0.02, 0.06
+    keys = np.array([[x, y, z] for x in range(-2, 3) for y in range(-2, 2) for z in range(3, 7)], np.int32)
+    keys = keys[rng.uniform(size=len(keys)) >= absent]
+    shape = (len(keys), 512)
+    sdf = rng.uniform(-tau, tau, shape)
+    sdf = np.where(rng.uniform(size=shape) < density, sdf, tau)    # the rest: free space
+    sdf[rng.uniform(size=shape) < 0.01] = 0.0
+    sdf[rng.uniform(size=shape) < 0.01] = -tau
+    w = (rng.uniform(size=shape) >= holes).astype(np.float32)
+    rgb = np.zeros(shape + (3,), np.uint8)
+    m = rf.Map(rf.MapParams(s, tau, 5.0, 1 << 12, 1 << 10, 255, 4, storage, 64 * 48))
+    m.import_(torch.from_numpy(keys).cuda(), torch.from_numpy(sdf.astype(np.float32)).cuda(),
+              torch.from_numpy(w).cuda(), torch.from_numpy(rgb).cuda())
+    ke, se, we, ce = [t.cpu().numpy() for t in m.export()]          # as stored
+    o32 = O.OracleMap(s, tau, 5.0, 255, 4, real_bits=32, storage=orc_storage)
+    o32.import_(ke, se.astype(np.float64), we.astype(np.float64), ce)
+    g, t32 = m.mesh().cpu().numpy(), o32.mesh()
+    assert len(g) == len(t32) and (len(g) > 0) == (density >= 0.5)  # 2%: no cube has all corners in the band
+    assert np.array_equal(sorted_tris(g), sorted_tris(t32))
+    assert np.array_equal(m.mesh().cpu().numpy(), g)
+    f = rf.Frame(torch.full((48, 64), 0.9, dtype=torch.float32, device="cuda"),
+                 torch.zeros((48, 64, 3), dtype=torch.uint8, device="cuda"), 60.0, 60.0, 31.5, 23.5, 1.0)
+    fresh = rf.Map(m.params)
+    lists = []
+    for q in (m, fresh):
+        q.allocate(f, dev_pose(np.eye(4)))
+        k = q.frame_blocks().cpu().numpy()
+        lists.append(k[np.lexsort(k.T)])
+    assert np.array_equal(lists[0], lists[1])
+
+
+def test_mesh_of_many_blocks(rf):
+    """More blocks than a workgroup of the write pass lists at once: the
+    surface's blocks among 530 000 of free space give the same triangles."""
+    s, tau = 0.01, 0.05
+    c = np.array([0.3, 0.2, 0.1])
+    keys, sdf, w, rgb = sphere_inputs(c, 0.15, s, tau)
+    arr = [torch.from_numpy(x).cuda() for x in (keys, sdf.astype(np.float32), w.astype(np.float32), rgb)]
+    small = rf.Map(rf.MapParams(s, tau, 5.0, 1 << 12, 1 << 11, 255, 4, "fp16", 64 * 64))
+    small.import_(*arr)
+    n = 530000
+    m = rf.Map(rf.MapParams(s, tau, 5.0, 1 << 21, n + (1 << 12), 255, 4, "fp16", 64 * 64))
+    grid = torch.arange(n, device="cuda", dtype=torch.int32)
+    far = torch.stack([100 + grid % 100, 100 + (grid // 100) % 100, 100 + grid // 10000], 1).contiguous()
+    half = n // 2
+    tau_block = torch.full((half, 512), tau, dtype=torch.float32, device="cuda")
+    one = torch.ones((half, 512), dtype=torch.float32, device="cuda")
+    black = torch.zeros((half, 512, 3), dtype=torch.uint8, device="cuda")
+    m.import_(far[:half], tau_block, one, black)
+    m.import_(*arr)
+    m.import_(far[half:2 * half], tau_block, one, black)
+    a, b = small.mesh().cpu().numpy(), m.mesh().cpu().numpy()
+    assert len(a) == len(b) > 5000
+    assert np.array_equal(sorted_tris(a), sorted_tris(b))
