@@ -3,10 +3,10 @@
 // One launch per Gauss-Newton/LM iteration, one thread per pixel of the
 // pyramid level (a workgroup covers a 16x16 pixel tile, so the voxels its
 // wavefronts gather are close together).  A thread forms the depth residual S and the photometric
-// residual Iv - I with their 6-DoF Jacobians in FP32 and parks them in LDS;
-// the workgroup then forms the 29 normal-equation terms in FP64 (products of
-// FP32 factors are exact in FP64) with a fixed-order transposed reduction
-// over its pixels, and adds them to device-wide accumulators.
+// residual Iv - I with their 6-DoF Jacobians in FP32 and, from them, its
+// pixel's 29 normal-equation terms in FP64 (products of FP32 factors are exact
+// in FP64); each wavefront adds its terms up in a fixed order, and the
+// workgroup adds the wavefronts' sums to device-wide accumulators.
 //
 // The accumulators are fixed point (units of 2^-60) held as two chunks in
 // 64-bit words, the low 48 bits and the signed rest, and summed with
@@ -36,8 +36,7 @@ constexpr double kFixScale = 0x1p60;
 constexpr int kTermWords = 16;                     // one 128-byte line per term
 constexpr int kCopyWords = kNE * kTermWords;       // one copy of the 29 accumulators
 constexpr int kBufWords = kAccCopies * kCopyWords;  // one accumulator buffer
-constexpr int kTerms = 15;                         // J_d(6) J_c(6) r_d r_c used
-constexpr int kGroups = kTrackBlock / 32;          // LDS reduction groups per term
+constexpr int kTerms = 14;                         // J_d(6) J_c(6) r_d r_c
 constexpr int kTileW = kTrackBlock / 16;           // pixel tile: kTileW x 16
 
 struct TrackArgs {
@@ -564,13 +563,104 @@ __device__ __forceinline__ void build_tile_cache(const BlockRef* tab, const uint
   }
 }
 
+// Normal-equation sums of a wavefront.  Each lane forms the 28 products of its
+// pixel in FP64 (products of FP32 factors are exact; the 29th term, the count,
+// is a ballot), and the wavefront adds them up by exchanging halves: a step
+// over lane bit b gives half of the terms to the lanes with the bit set and
+// half to the others, adding the partner's, so 28 terms take 14 + 7 + 4 + 2 + 1
+// additions (and one plain one) instead of 28 x 6.  The last lane bit is
+// summed plainly, so pairs of lanes end with the same term.  Parking the
+// factors in LDS for 232 threads to sum took 116 LDS reads a pixel and a second
+// barrier: registration of 160x120 229 -> 212 us, 640x480 454 -> 432 us, eight
+// mixed sessions a step 3145 -> 3069 us.
+__device__ __forceinline__ void f64_words(double v, uint32_t& lo, uint32_t& hi) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  lo = (uint32_t)b;
+  hi = (uint32_t)(b >> 32);
+}
+__device__ __forceinline__ double f64_of(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// a in the lower 32 lanes plus a in the upper ones (lower lanes), likewise b
+// (upper lanes); ROWS: the same between the even and odd rows of 16 lanes.
+template <bool ROWS>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  uint32_t al, ah, bl, bh;
+  f64_words(a, al, ah);
+  f64_words(b, bl, bh);
+  if constexpr (ROWS) {
+    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return f64_of(l[0], h[0]) + f64_of(l[1], h[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return f64_of(l[0], h[0]) + f64_of(l[1], h[1]);
+  }
+}
+// The value of the lane that DPP control CTRL pairs with this one.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  uint32_t lo, hi;
+  f64_words(v, lo, hi);
+  lo = __builtin_amdgcn_update_dpp(0u, lo, CTRL, 0xF, 0xF, false);
+  hi = __builtin_amdgcn_update_dpp(0u, hi, CTRL, 0xF, 0xF, false);
+  return f64_of(lo, hi);
+}
+// a over both lanes of a pair for the lanes with bit clear, b for the others;
+// CTRL pairs every lane with one whose bit differs.
+template <int CTRL>
+__device__ __forceinline__ double pair_add(double a, double b, bool bit) {
+  const double keep = bit ? b : a, send = bit ? a : b;
+  return keep + dpp_f64<CTRL>(send);
+}
+constexpr int kRowMirror = 0x140, kHalfMirror = 0x141, kQuadHalves = 0x4E, kQuadPairs = 0xB1;
+
+// Packed upper triangle: row and column of H's term k < 21.
+__host__ __device__ constexpr int ne_row(int k) { return k < 6 ? 0 : (k < 11 ? 1 : (k < 15 ? 2 : (k < 18 ? 3 : (k < 20 ? 4 : 5)))); }
+__host__ __device__ constexpr int ne_col(int k) {
+  return k - (6 * ne_row(k) - (ne_row(k) * (ne_row(k) - 1)) / 2) + ne_row(k);
+}
+
+// The wavefront's sum of one term for every lane: term index in *k (28 and
+// over: none).  t: J_d(6) J_c(6) r_d r_c of the lane's pixel, zeros without one.
+__device__ __forceinline__ double wave_sums(const float t[14], double w_c, int lane, int* k) {
+  double d[7], c[7];  // J and the residual
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    d[i] = (double)t[i < 6 ? i : 12];
+    c[i] = (double)t[i < 6 ? 6 + i : 13];
+  }
+  // term q: H (21), g (6), cost; row by row, so that few values are live at once
+  auto term = [&](int q) {
+    const int r = q < 21 ? ne_row(q) : (q < 27 ? q - 21 : 6), l = q < 21 ? ne_col(q) : 6;
+    return fma(w_c * c[r], c[l], d[r] * d[l]);
+  };
+  double b[8];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    const double a0 = swap_add<false>(term(4 * i), term(4 * i + 1)), a1 = swap_add<false>(term(4 * i + 2), term(4 * i + 3));
+    b[i] = swap_add<true>(a0, a1);
+  }
+  b[7] = 0.0;
+  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+  double e[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e[i] = pair_add<kRowMirror>(b[2 * i], b[2 * i + 1], b3);
+  const double g0 = pair_add<kHalfMirror>(e[0], e[1], b2), g1 = pair_add<kHalfMirror>(e[2], e[3], b2);
+  double v = pair_add<kQuadHalves>(g0, g1, b1);
+  v += dpp_f64<kQuadPairs>(v);
+  // undo the halvings: bit 5 picked the lowest bit of the index, then 4, 3, 2, 1
+  *k = ((lane >> 5) & 1) | ((lane >> 4) & 1) << 1 | ((lane >> 3) & 1) << 2 | ((lane >> 2) & 1) << 3 | ((lane >> 1) & 1) << 4;
+  return v;
+}
+
 // SLOTS: pairs the tile cache holds in LDS (256 at levels 0-1, 512 at the
 // coarser levels, whose few tiles each touch more blocks; more LDS and
 // registers there cost nothing, since those launches have few workgroups).
 template <int DF, int STORAGE, bool LM, int SLOTS>
 __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a) {
-  __shared__ float s_t[kTerms][kTrackBlock + 1];
-  __shared__ double s_g[kNE][kGroups + 1];
+  __shared__ double s_g[kTrackBlock / 64][kNE];  // per wavefront: its sums of the terms
   __shared__ double s_ne[kNE];
   __shared__ double s_nc[kLmWords];
   __shared__ double s_st[kLmWords];
@@ -721,7 +811,8 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
   if (stopped || s_state != 0) return;  // stopped or degenerate: pose kept, the pass stops
   const TileCache<SLOTS> cache{s_hk, s_hs, s_used, s_grid, s_gused, s_org[0], s_org[1], s_org[2]};
 
-  float term[kTerms];
+  float term[kTerms];  // J_d(6) J_c(6) r_d r_c
+  bool counts = false;
 #pragma unroll
   for (int k = 0; k < kTerms; ++k) term[k] = 0.0f;
   if (inside && depth_ok(D, m.dmax) && !(mask && mk_raw)) {
@@ -752,11 +843,16 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
       term[11] = y[0] * gI[1] - y[1] * gI[0];
       term[12] = S;
       term[13] = Iv - Ipix;
-      term[14] = 1.0f;
+      counts = true;
     }
   }
-#pragma unroll
-  for (int k = 0; k < kTerms; ++k) s_t[k][threadIdx.x] = term[k];
+  {
+    int k;
+    const double v = wave_sums(term, (double)a.w_c, lane, &k);
+    const unsigned long long cb = __ballot(counts);
+    if (!(lane & 1) && k < 28) s_g[wave][k] = v;
+    if (lane == 0) s_g[wave][28] = (double)__popcll(cb);
+  }
   __syncthreads();
   // the pairs used in this launch become the tile's cache for the next one
   if (cached) {
@@ -778,44 +874,12 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
     }
   }
 
-  // thread (k, g) sums term k over pixels g, g + kGroups, ... in a fixed order
-  // as a depth and a photometric product chain.  Every term has the same
-  // shape (the count is the sum of 1 x 1 with a zero photometric weight), so
-  // the wavefronts do not diverge, and the loop is unrolled so its LDS reads
-  // are issued ahead of the FMAs.
-  const double wc = (double)a.w_c;
-  if (threadIdx.x < kNE * kGroups) {
-    const int k = threadIdx.x % kNE, g = threadIdx.x / kNE;
-    int r = 0, c = 12;
-    if (k < 21) {
-      int kk = k;
-      while (kk >= 6 - r) {
-        kk -= 6 - r;
-        ++r;
-      }
-      c = r + kk;
-    } else if (k < 27) {
-      r = k - 21;
-    }
-    // k < 21: H(r, c); k < 27: g(r); 27: cost; 28: count
-    const int rd = (k < 27) ? r : (k == 27 ? 12 : 14), cd = (k < 21) ? c : (k < 28 ? 12 : 14);
-    const int rc = (k < 27) ? 6 + r : (k == 27 ? 13 : 14), cc = (k < 21) ? 6 + c : (k < 28 ? 13 : 14);
-    const double wk = (k < 28) ? wc : 0.0;
-    double acc_d = 0.0, acc_c = 0.0;
-#pragma unroll
-    for (int i = 0; i < kTrackBlock / kGroups; ++i) {
-      const int p = g + i * kGroups;
-      acc_d = fma((double)s_t[rd][p], (double)s_t[cd][p], acc_d);
-      acc_c = fma((double)s_t[rc][p], (double)s_t[cc][p], acc_c);
-    }
-    s_g[k][g] = acc_d + wk * acc_c;
-  }
   __syncthreads();
   if (cached && threadIdx.x == 0) *tcount = min(s_nref, (uint32_t)nrefs);
   if (threadIdx.x < kNE) {
     double tot = 0.0;
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) tot += s_g[threadIdx.x][g];
+    for (int w = 0; w < kTrackBlock / 64; ++w) tot += s_g[w][threadIdx.x];
     if (!fixed_add(acc_buf(m, a.acc_write) + (g0 % kAccCopies) * kCopyWords + threadIdx.x * kTermWords, tot)) {
       atomicOr(&m.st->flags, (uint32_t)RF_FLAG_TRACK_RANGE);
       if (stats) atomicOr(&stats->flags, (uint32_t)RF_FLAG_TRACK_RANGE);
