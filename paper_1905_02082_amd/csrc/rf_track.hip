@@ -384,6 +384,7 @@ struct TileCache {
   uint8_t* used;            // SLOTS, 1 when looked up in this launch
   int* grid;                // kWin^3 window of block slots (kNoSlot: unknown)
   uint8_t* gused;           // kWin^3, 1 when looked up in this launch
+  int* miss;                // set when a lookup went to the hash table
   int ax, ay, az;           // window origin (block coordinates)
 
   // window cell of block (x,y,z), or -1 outside the window
@@ -472,6 +473,7 @@ struct CachedSlots {
       b0.slot = bslot[k];
       const unsigned long long key = pack_key(x, y, z);
       sl[k] = resolve_slot(m, b0, key, hash3(x, y, z) & m.bucket_mask);
+      *c.miss = 1;
       const int cl = c.cell(x, y, z);
       if (cl >= 0) {
         c.grid[cl] = sl[k];
@@ -490,76 +492,171 @@ struct CachedSlots {
   }
 };
 
-// Wavefront 1 of a residual workgroup (the tracking kernel runs the same
-// steps inline): the tile's cached block pairs (tiles without a cache entry
-// start from an empty table) placed in the direct-mapped window around their
-// bounding box or in the LDS hash.
+// LDS of a tile's cache and the wavefront that fills it: the tile's cached
+// block pairs (tiles without a cache entry start from an empty table) placed
+// in the direct-mapped window or in the LDS hash.  Entry 0 of a tile's pairs
+// holds the window's origin, set when the pairs were written.
+template <int SLOTS>
+struct CacheLds {
+  alignas(16) unsigned long long hk[SLOTS];
+  alignas(16) int hs[SLOTS];
+  alignas(16) uint8_t used[SLOTS];
+  alignas(16) int grid[kWinCells];
+  alignas(16) uint8_t gused[kWinCells];
+  int org[3];
+  int miss;
+  int cnt;               // pairs loaded
+  uint32_t nref;         // pairs written back
+  uint32_t cells;        // their bounding box: the window's x, y and z in use (8 bits each),
+  int lo[3], hi[3];      // and the blocks outside the window
+
+  __device__ __forceinline__ TileCache<SLOTS> cache(int ax, int ay, int az) {
+    return TileCache<SLOTS>{hk, hs, used, grid, gused, &miss, ax, ay, az};
+  }
+};
+
 template <int SLOTS>
 __device__ __forceinline__ void build_tile_cache(const BlockRef* tab, const uint32_t* tcount, bool cached, int nrefs,
-                                                 uint32_t epoch, int lane, unsigned long long* s_hk, int* s_hs,
-                                                 uint8_t* s_used, int* s_grid, uint8_t* s_gused, int* s_org,
-                                                 uint32_t* s_nref) {
+                                                 uint32_t epoch, int lane, CacheLds<SLOTS>& L) {
   const BlockRef none{kEmptyKey, -1, 0u};
   constexpr int kLoads = SLOTS / 64;
-  const int cnt = cached ? (int)min(*tcount, (uint32_t)nrefs) : 0;
+  const int cnt = cached ? (int)min(*tcount, (uint32_t)(nrefs - 1)) : 0;
   BlockRef e[kLoads];
 #pragma unroll
   for (int q = 0; q < kLoads; ++q) e[q] = (cached && lane + 64 * q < nrefs) ? tab[lane + 64 * q] : none;
+  // clear with the widest stores
 #pragma unroll
-  for (int q = 0; q < SLOTS / 64; ++q) {
-    s_hk[lane + 64 * q] = kEmptyKey;
-    s_hs[lane + 64 * q] = kNoSlot;
-    s_used[lane + 64 * q] = 0;
+  for (int q = 0; q < SLOTS / 128; ++q)
+    reinterpret_cast<ulonglong2*>(L.hk)[lane + 64 * q] = make_ulonglong2(kEmptyKey, kEmptyKey);
+#pragma unroll
+  for (int q = 0; q < SLOTS / 256; ++q) {
+    reinterpret_cast<int4*>(L.hs)[lane + 64 * q] = make_int4(kNoSlot, kNoSlot, kNoSlot, kNoSlot);
+    reinterpret_cast<uint32_t*>(L.used)[lane + 64 * q] = 0u;
   }
 #pragma unroll
-  for (int q = 0; q < kWinCells / 64; ++q) {
-    s_grid[lane + 64 * q] = kNoSlot;
-    s_gused[lane + 64 * q] = 0;
+  for (int q = 0; q < kWinCells / 256; ++q) {
+    reinterpret_cast<int4*>(L.grid)[lane + 64 * q] = make_int4(kNoSlot, kNoSlot, kNoSlot, kNoSlot);
+    reinterpret_cast<uint32_t*>(L.gused)[lane + 64 * q] = 0u;
   }
-  if (lane == 0) *s_nref = 0u;
-  // window origin: centre of the bounding box of the valid cached blocks
-  bool v[kLoads];
-  int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
-#pragma unroll
-  for (int q = 0; q < kLoads; ++q) {
-    v[q] = lane + 64 * q < cnt && e[q].key != kEmptyKey && (e[q].slot >= 0 || e[q].epoch == epoch);
-    int p[3];
-    unpack_key(e[q].key, p[0], p[1], p[2]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = min(lo[d], v[q] ? p[d] : INT_MAX);
-      hi[d] = max(hi[d], v[q] ? p[d] : INT_MIN);
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = min(lo[d], __shfl_xor(lo[d], o));
-      hi[d] = max(hi[d], __shfl_xor(hi[d], o));
-    }
-  }
-  const bool any = lo[0] <= hi[0];
+  // the window's origin (entry 0)
   int org[3];
+  unpack_key(((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(e[0].key >> 32)) << 32) |
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)e[0].key),
+             org[0], org[1], org[2]);
 #pragma unroll
-  for (int d = 0; d < 3; ++d) org[d] = any ? ((lo[d] + hi[d]) >> 1) - (kWin / 2 - 1) : kFarOrigin;
+  for (int d = 0; d < 3; ++d)
+    if (cnt == 0) org[d] = kFarOrigin;
   if (lane == 0) {
-    s_org[0] = org[0];
-    s_org[1] = org[1];
-    s_org[2] = org[2];
+    L.miss = 0;
+    L.cnt = cnt;
+    L.nref = L.cells = 0u;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      L.org[d] = org[d];
+      L.lo[d] = INT_MAX;
+      L.hi[d] = INT_MIN;
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const TileCache<SLOTS> wc{s_hk, s_hs, s_used, s_grid, s_gused, org[0], org[1], org[2]};
+  const TileCache<SLOTS> wc = L.cache(org[0], org[1], org[2]);
 #pragma unroll
   for (int q = 0; q < kLoads; ++q) {
-    if (!v[q]) continue;
+    const int i = lane + 64 * q;
+    if (!(i >= 1 && i <= cnt && e[q].key != kEmptyKey && (e[q].slot >= 0 || e[q].epoch == epoch))) continue;
     int p[3];
     unpack_key(e[q].key, p[0], p[1], p[2]);
     const int cl = wc.cell(p[0], p[1], p[2]);
-    if (cl >= 0) s_grid[cl] = e[q].slot;
+    if (cl >= 0) L.grid[cl] = e[q].slot;
     else wc.insert(p[0], p[1], p[2], e[q].key, e[q].slot, false);
+  }
+}
+
+// The pairs used in this launch become the tile's cache for the next one, and
+// the centre of their bounding box its window's.  Called by the whole workgroup
+// after a lookup missed; otherwise the cache stays as it is, which spares most
+// launches the pass over the window, and every launch the search for the
+// window's place that used to come before the pairs were placed.
+template <int SLOTS>
+__device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount, int nrefs, uint32_t epoch,
+                                                 CacheLds<SLOTS>& L) {
+  const int lane = threadIdx.x & 63;
+  // one position counter atomic per wavefront
+  auto keep = [&](bool yes, unsigned long long key, int slot) {
+    const unsigned long long bal = __ballot(yes);
+    if (bal == 0ull) return;  // uniform
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(&L.nref, (uint32_t)__popcll(bal));
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + 1u;
+    const uint32_t pos =
+        base + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+    if (yes && pos < (uint32_t)nrefs) tab[pos] = BlockRef{key, slot, epoch};
+  };
+  // Pairs not used in this launch stay too while the tile has few: the steps of
+  // a registration come by the same blocks in the next one.  Those in the
+  // window stay below half of the room; those outside are costlier to place
+  // (the LDS hash), and a tile of the coarsest level at 0.5 cm has up to 230, so
+  // they stay below a quarter.  640x480 at 1 cm / 0.5 cm, whole frame: none kept
+  // 954 / 1216 us, all below half 929 / 1280, window only 948 / 1205, this rule
+  // 933 / 1202.
+  const bool all = 2 * L.cnt < nrefs, few = 4 * L.cnt < nrefs;
+  // the window's cells in use, a bit per x, y and z
+  uint32_t cells = 0;
+#pragma unroll
+  for (int q = 0; q < kWinCells / kTrackBlock; ++q) {
+    const int h = threadIdx.x + q * kTrackBlock;
+    const int ss = L.grid[h], x = h % kWin, y = (h / kWin) % kWin, z = h / (kWin * kWin);
+    const bool yes = ss != kNoSlot && L.gused[h];
+    keep(yes || (all && ss != kNoSlot), pack_key(L.org[0] + x, L.org[1] + y, L.org[2] + z), ss);
+    if (yes) cells |= 1u << x | 256u << y | 65536u << z;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) cells |= (uint32_t)__shfl_xor((int)cells, o);
+  if (lane == 0 && cells) atomicOr(&L.cells, cells);
+  for (int h0 = 0; h0 < SLOTS; h0 += kTrackBlock) {
+    const int h = h0 + threadIdx.x;
+    const unsigned long long kk = L.hk[h];
+    const int ss = L.hs[h];
+    const bool known = kk != kEmptyKey && ss != kNoSlot, yes = known && L.used[h];
+    keep(yes || (few && known), kk, ss);
+    const unsigned long long bal = __ballot(yes);
+    if (bal == 0ull) continue;  // uniform
+    // their bounding box, relative to one of them (16 bits are plenty: it only
+    // centres a window): the minimum of d and of -d together
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    const int first = __ffsll((long long)bal) - 1;
+    int p[3];
+    unpack_key(kk, p[0], p[1], p[2]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int ref = __builtin_amdgcn_readlane(p[d], first);
+      const int off = yes ? max(-32767, min(32767, p[d] - ref)) : 0;
+      short2v v = {(short)off, (short)-off};
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const int w = __shfl_xor(__builtin_bit_cast(int, v), o);
+        v = __builtin_elementwise_min(v, __builtin_bit_cast(short2v, w));
+      }
+      if (lane == 0) {
+        atomicMin(&L.lo[d], ref + v.x);
+        atomicMax(&L.hi[d], ref - v.y);
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t n = min(L.nref, (uint32_t)(nrefs - 1));
+    *tcount = n;
+    int org[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const uint32_t c = (L.cells >> (8 * d)) & 255u;
+      const int lo = min(L.lo[d], c ? L.org[d] + __ffs((int)c) - 1 : INT_MAX);
+      const int hi = max(L.hi[d], c ? L.org[d] + 31 - __clz((int)c) : INT_MIN);
+      org[d] = n ? ((lo + hi) >> 1) - (kWin / 2 - 1) : 0;
+    }
+    tab[0] = BlockRef{pack_key(org[0], org[1], org[2]), 0, epoch};
   }
 }
 
@@ -666,13 +763,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
   __shared__ double s_st[kLmWords];
   __shared__ double s_T[16];
   __shared__ int s_state;
-  __shared__ unsigned long long s_hk[SLOTS];
-  __shared__ int s_hs[SLOTS];
-  __shared__ uint8_t s_used[SLOTS];
-  __shared__ int s_grid[kWinCells];
-  __shared__ uint8_t s_gused[kWinCells];
-  __shared__ int s_org[3];
-  __shared__ uint32_t s_nref;
+  __shared__ CacheLds<SLOTS> s_cache;
   const int jb = batch_job(b, blockIdx.x);
   const Job& J = b.job[jb];
   const MapDev& m = J.m;
@@ -719,76 +810,11 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
                   (size_t)(cached ? g0 : 0) * tile_refs(cached ? a.level : 0);
   uint32_t* tcount = m.tc_count + (size_t)(cached ? a.level : 0) * m.tc_tiles + (cached ? g0 : 0);
   const int nrefs = tile_refs(a.level);
-  // (the steps of build_tile_cache, written out: calling it here changed the
-  // kernel's instruction schedule and cost the large rooms' tracking 3%)
   // the solving wavefront (and the cache builder after it) rotate with the
   // tile index, so the solves of the workgroups sharing a CU spread over its
   // SIMDs
   const int sw = g0 & 3, cw = (sw + 1) & 3;
-  if (wave == cw) {
-    const BlockRef none{kEmptyKey, -1, 0u};
-    constexpr int kLoads = SLOTS / 64;
-    const int cnt = cached ? (int)min(*tcount, (uint32_t)nrefs) : 0;
-    BlockRef e[kLoads];
-#pragma unroll
-    for (int q = 0; q < kLoads; ++q) e[q] = (cached && lane + 64 * q < nrefs) ? tab[lane + 64 * q] : none;
-#pragma unroll
-    for (int q = 0; q < SLOTS / 64; ++q) {
-      s_hk[lane + 64 * q] = kEmptyKey;
-      s_hs[lane + 64 * q] = kNoSlot;
-      s_used[lane + 64 * q] = 0;
-    }
-#pragma unroll
-    for (int q = 0; q < kWinCells / 64; ++q) {
-      s_grid[lane + 64 * q] = kNoSlot;
-      s_gused[lane + 64 * q] = 0;
-    }
-    if (lane == 0) s_nref = 0u;
-    // window origin: centre of the bounding box of the valid cached blocks
-    bool v[kLoads];
-    int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
-#pragma unroll
-    for (int q = 0; q < kLoads; ++q) {
-      v[q] = lane + 64 * q < cnt && e[q].key != kEmptyKey && (e[q].slot >= 0 || e[q].epoch == epoch);
-      int p[3];
-      unpack_key(e[q].key, p[0], p[1], p[2]);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        lo[d] = min(lo[d], v[q] ? p[d] : INT_MAX);
-        hi[d] = max(hi[d], v[q] ? p[d] : INT_MIN);
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        lo[d] = min(lo[d], __shfl_xor(lo[d], o));
-        hi[d] = max(hi[d], __shfl_xor(hi[d], o));
-      }
-    }
-    const bool any = lo[0] <= hi[0];
-    int org[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) org[d] = any ? ((lo[d] + hi[d]) >> 1) - (kWin / 2 - 1) : kFarOrigin;
-    if (lane == 0) {
-      s_org[0] = org[0];
-      s_org[1] = org[1];
-      s_org[2] = org[2];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const TileCache<SLOTS> wc{s_hk, s_hs, s_used, s_grid, s_gused, org[0], org[1], org[2]};
-#pragma unroll
-    for (int q = 0; q < kLoads; ++q) {
-      if (!v[q]) continue;
-      int p[3];
-      unpack_key(e[q].key, p[0], p[1], p[2]);
-      const int cl = wc.cell(p[0], p[1], p[2]);
-      if (cl >= 0) s_grid[cl] = e[q].slot;
-      else wc.insert(p[0], p[1], p[2], e[q].key, e[q].slot, false);
-    }
-  }
+  if (wave == cw) build_tile_cache<SLOTS>(tab, tcount, cached, nrefs, epoch, lane, s_cache);
   if (wave == sw) {
     if (a.solve) {
       solve_step<LM>(m, user_pose, a, stats, s_ne, s_T, &s_state, g0 == 0, stopped != 0, false, s_nc, s_st);
@@ -809,7 +835,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
   }
   __syncthreads();
   if (stopped || s_state != 0) return;  // stopped or degenerate: pose kept, the pass stops
-  const TileCache<SLOTS> cache{s_hk, s_hs, s_used, s_grid, s_gused, s_org[0], s_org[1], s_org[2]};
+  const TileCache<SLOTS> cache = s_cache.cache(s_cache.org[0], s_cache.org[1], s_cache.org[2]);
 
   float term[kTerms];  // J_d(6) J_c(6) r_d r_c
   bool counts = false;
@@ -854,28 +880,6 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
     if (lane == 0) s_g[wave][28] = (double)__popcll(cb);
   }
   __syncthreads();
-  // the pairs used in this launch become the tile's cache for the next one
-  if (cached) {
-    for (int h = threadIdx.x; h < kWinCells; h += kTrackBlock) {
-      const int ss = s_grid[h];
-      if (ss != kNoSlot && s_gused[h]) {
-        const uint32_t pos = atomicAdd(&s_nref, 1u);
-        const unsigned long long kk = pack_key(cache.ax + h % kWin, cache.ay + (h / kWin) % kWin, cache.az + h / (kWin * kWin));
-        if (pos < (uint32_t)nrefs) tab[pos] = BlockRef{kk, ss, epoch};
-      }
-    }
-    for (int h = threadIdx.x; h < SLOTS; h += kTrackBlock) {
-      const unsigned long long kk = s_hk[h];
-      const int ss = s_hs[h];
-      if (kk != kEmptyKey && ss != kNoSlot && s_used[h]) {
-        const uint32_t pos = atomicAdd(&s_nref, 1u);
-        if (pos < (uint32_t)nrefs) tab[pos] = BlockRef{kk, ss, epoch};
-      }
-    }
-  }
-
-  __syncthreads();
-  if (cached && threadIdx.x == 0) *tcount = min(s_nref, (uint32_t)nrefs);
   if (threadIdx.x < kNE) {
     double tot = 0.0;
 #pragma unroll
@@ -885,6 +889,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
       if (stats) atomicOr(&stats->flags, (uint32_t)RF_FLAG_TRACK_RANGE);
     }
   }
+  if (cached && s_cache.miss) write_tile_cache<SLOTS>(tab, tcount, nrefs, epoch, s_cache);  // uniform
 }
 
 // Residual of the dynamic mask (Sec. III-C): r = S(T x)^2 of every valid
@@ -896,13 +901,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
 // lookups.
 template <int DF, int STORAGE, int SLOTS>
 __global__ __launch_bounds__(kTrackBlock) void residual_kernel(Batch b, float gamma) {
-  __shared__ unsigned long long s_hk[SLOTS];
-  __shared__ int s_hs[SLOTS];
-  __shared__ uint8_t s_used[SLOTS];
-  __shared__ int s_grid[kWinCells];
-  __shared__ uint8_t s_gused[kWinCells];
-  __shared__ int s_org[3];
-  __shared__ uint32_t s_nref;
+  __shared__ CacheLds<SLOTS> s_cache;
   const int jb = batch_job(b, blockIdx.x);
   const Job& J = b.job[jb];
   const MapDev& m = J.m;
@@ -919,10 +918,9 @@ __global__ __launch_bounds__(kTrackBlock) void residual_kernel(Batch b, float ga
   const BlockRef* tab = m.tcache + (size_t)(cached ? g0 : 0) * tile_refs(0);
   const uint32_t* tcount = m.tc_count + (cached ? g0 : 0);
   if (wave == 1)
-    build_tile_cache<SLOTS>(tab, tcount, cached, tile_refs(0), m.st->epoch, lane, s_hk, s_hs, s_used, s_grid,
-                            s_gused, s_org, &s_nref);
+    build_tile_cache<SLOTS>(tab, tcount, cached, tile_refs(0), m.st->epoch, lane, s_cache);
   __syncthreads();
-  const TileCache<SLOTS> cache{s_hk, s_hs, s_used, s_grid, s_gused, s_org[0], s_org[1], s_org[2]};
+  const TileCache<SLOTS> cache = s_cache.cache(s_cache.org[0], s_cache.org[1], s_cache.org[2]);
   uint8_t out = 0;
   float r = -1.0f;
   if (inside && depth_ok(D, m.dmax)) {

@@ -64,3 +64,31 @@ def test_block_cache_never_changes_results(rf, storage):
     build(rf, ref, seq, range(3, 7))
     for x, y in zip(track(rf, warm, seq, 7, 6), track(rf, ref, seq, 7, 6)):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("voxel,tau,adaptive", [(0.004, 0.02, False), (0.01, 0.03, True), (0.02, 0.06, False)])
+def test_block_cache_over_jumping_frames(rf, voxel, tau, adaptive):
+    """Tiles with more blocks than a cache entry holds and blocks outside its
+    window (depth steps at small voxels), pairs kept over several launches,
+    and frames from poses far apart in turn: a warm map's registrations equal
+    those of a map that has tracked nothing before."""
+    seq = synth.static_room(n_frames=61, width=320, height=240)
+    mp = map_params(rf, seq, max_blocks=1 << 18)
+    mp.voxel_size, mp.truncation = voxel, tau
+    warm = rf.Map(mp)
+    build(rf, warm, seq, (0, 30, 60))
+    tp = rf.TrackParams(4, 5, adaptive=adaptive)
+
+    def run(m, k, start):
+        P = torch.as_tensor(seq.poses[start]).cuda().contiguous()
+        m.track(gpu_frame(rf, seq, k), P, tp)
+        out = m.normal_equations(gpu_frame(rf, seq, k), P, level=0)
+        return P.cpu().numpy(), out.cpu().numpy()
+
+    for k, start in ((30, 31), (60, 59), (0, 1), (60, 58), (30, 29)):
+        a = run(warm, k, start)
+        fresh = rf.Map(mp)
+        build(rf, fresh, seq, (0, 30, 60))
+        b = run(fresh, k, start)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert a[1][28] > 1000
