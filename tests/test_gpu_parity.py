@@ -91,6 +91,42 @@ def test_allocation_block_set_bit_exact(rf, room):
     assert np.array_equal(gk, o.export()[0])
 
 
+@pytest.mark.parametrize("W,H,stride,voxel,tau,dmax,free", [
+    (1, 1, 1, 0.02, 0.06, 5.0, False), (17, 9, 1, 0.02, 0.06, 5.0, True), (33, 31, 3, 0.004, 0.05, 3.0, False),
+    (65, 33, 5, 0.003, 0.01, 5.0, False), (130, 70, 64, 0.01, 0.03, 2.0, True), (129, 47, 2, 0.02, 0.06, 1.0, False),
+    (64, 64, 4, 0.01, 0.03, 3.0, False),
+])
+def test_allocated_blocks_over_ray_shapes(rf, W, H, stride, voxel, tau, dmax, free):
+    """Ragged ray tiles, every pixel and few pixels casting carve rays, rays of
+    several walked chunks, bands of many blocks, measurements beyond the
+    clipping plane, masked and unmeasured pixels, neighbouring rays in and out
+    of step, and a camera off the origin: the frame's blocks and the map's are
+    those of the FP32 mirror, frame after frame."""
+    rng = np.random.default_rng(W * 100 + H)
+    f = 0.8 * max(W, 24)
+    intr = (f, f, (W - 1) / 2.0, (H - 1) / 2.0)
+    rgb = rng.integers(0, 255, (H, W, 3)).astype(np.uint8)
+    m = rf.Map(rf.MapParams(voxel, tau, dmax, 1 << 18, 1 << 15, 255, stride, "fp16", W * H, free))
+    o = O.OracleMap(voxel, tau, dmax, 255, stride, real_bits=32, storage=1, free_blocks=1 if free else 0)
+    uu, vv = np.meshgrid(np.arange(W), np.arange(H))
+    for k in range(3):
+        depth = 1.6 + 0.5 * np.sin(uu / 9.0 + k) * np.cos(vv / 7.0) + rng.normal(0, 0.002, (H, W))
+        depth = np.where(rng.uniform(size=(H, W)) < 0.1, rng.uniform(0.3, 4.0, (H, W)), depth)
+        depth = np.where(rng.uniform(size=(H, W)) < 0.05, 0.0, depth).astype(np.float32)
+        if k == 2:
+            depth = (depth * 1000.0).astype(np.uint16)             # the other depth format
+        mask = (rng.uniform(size=(H, W)) < 0.1).astype(np.uint8) if k else None
+        T = np.eye(4)
+        c, s = np.cos(0.3 + 0.2 * k), np.sin(0.3 + 0.2 * k)
+        T[:3, :3] = np.array([[c, 0, s], [0, 1, 0], [-s, 0, c]]) @ np.array([[1, 0, 0], [0, c, -s], [0, s, c]])
+        T[:3, 3] = [0.1 * k - 7.3, 0.02, 3.1]
+        g, fr = rf.Frame.from_numpy(depth, rgb, *intr), O.Frame(depth, rgb, *intr, depth_scale=0.001 if k == 2 else 1.0)
+        m.allocate(g, dev_pose(T), None if mask is None else torch.from_numpy(mask).cuda())
+        ref = o.allocate(fr, T, mask)
+        assert np.array_equal(gpu_keyset(m.frame_blocks()), ref), k
+    assert m.status()[0] == 0 and m.num_keys() == o.num_blocks
+
+
 # ---------------------------------------------------------------- integration
 
 def test_integration_matches_oracle(rf, room):
