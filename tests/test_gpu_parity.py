@@ -106,7 +106,7 @@ def test_allocated_blocks_over_ray_shapes(rf, W, H, stride, voxel, tau, dmax, fr
     f = 0.8 * max(W, 24)
     intr = (f, f, (W - 1) / 2.0, (H - 1) / 2.0)
     rgb = rng.integers(0, 255, (H, W, 3)).astype(np.uint8)
-    m = rf.Map(rf.MapParams(voxel, tau, dmax, 1 << 18, 1 << 15, 255, stride, "fp16", W * H, free))
+    m = rf.Map(rf.MapParams(voxel, tau, dmax, 1 << 18, 1 << 17, 255, stride, "fp16", W * H, free))
     o = O.OracleMap(voxel, tau, dmax, 255, stride, real_bits=32, storage=1, free_blocks=1 if free else 0)
     uu, vv = np.meshgrid(np.arange(W), np.arange(H))
     for k in range(3):
