@@ -261,7 +261,7 @@ rf_status hashmap_create(const rf_map_params* p, void* arena, size_t bytes, void
   d.rgb = reinterpret_cast<uchar4*>(a + L.rgb);
   d.partials = reinterpret_cast<double*>(a + L.partials);
   d.md = reinterpret_cast<uint8_t*>(a + L.md);
-  d.integ_counts = reinterpret_cast<uint4*>(a + L.counts);
+  d.integ_counts = reinterpret_cast<uint2*>(a + L.counts);
   d.cells = reinterpret_cast<float*>(a + L.cells);
   d.cells_cap = L.cells_cap;
   d.free_blocks = p->free_blocks ? 1u : 0u;

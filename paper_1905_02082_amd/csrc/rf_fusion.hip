@@ -11,10 +11,10 @@
 // frame's block list, each touched block once.
 //
 // Integration: workgroups stride over the listed blocks, 256 threads x 2
-// voxels per block, two blocks per step, each workgroup's list entries and
-// buckets read into LDS up front; only voxels the frame updates are
-// written.  Records are SoA per block, so a workgroup's loads and stores are
-// contiguous 4-KiB (FP32) / 2-KiB (FP16) runs.
+// neighbouring voxels per block, two blocks per step, each workgroup's list
+// entries and buckets read into LDS up front; only pairs with a voxel that the
+// frame updates are written.  Records are SoA per block, so a workgroup's loads
+// and stores are contiguous 4-KiB (FP32) / 2-KiB (FP16) runs.
 #include <type_traits>
 
 #include "rf_device.h"
@@ -617,11 +617,16 @@ __global__ __launch_bounds__(256) void classify_kernel(Batch b) {
 
 // Integration of one frame into the blocks of the frame list (Sec. III-A
 // running average, Sec. III-D carving).  Workgroups stride over the list and
-// take kIntegBlocks listed blocks per step; a thread owns voxels l and l + 256
+// take kIntegBlocks listed blocks per step; a thread owns voxels 2 t and 2 t + 1
 // of each.  A workgroup's list entries and buckets (uniform) are read into
 // LDS before its steps; a step issues the depth, the mask byte and the
-// voxel record of every voxel together before any is used.  The record is
-// read even for voxels the frame leaves untouched (about a fifth of a listed
+// voxel records (a pair per load) together before any is used.  What bounds it
+// is the vector arithmetic (80% of the issue slots at 0.5 cm: 37 k blocks, 19 M
+// voxels; the records' bytes alone would take 65 us): the divisions by a Newton
+// step from the hardware's reciprocal instead of the IEEE sequence and an LDS
+// table, block data kept in scalar registers, 24-bit pixel indices and counts by
+// ballot took 89 -> 81 us there, 26 -> 21.5 us at 1 cm, 50 -> 39 us on a compact
+// map.  The record is read even for voxels the frame leaves untouched (about a fifth of a listed
 // block), which costs those bytes but saves a dependent round trip; only
 // voxels the frame updates are written.
 constexpr int kIntegBlocks = 2;
@@ -649,14 +654,11 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
   float R[9], t[3];
   load_pose_f(J.pose, R, t);
   uint32_t nb = 0, nf = 0;
-  // correctly rounded reciprocals 1 / (W + 1) of the weights 0 .. 255
-  __shared__ float s_rw[256];
   // compact free space: per pending free block of the step, its voxels'
   // decisions (bit 0 some band update, bit 1 some voxel not carved) and the
   // pool slot it takes
   __shared__ uint32_t s_pf[kIntegBlocks];
   __shared__ uint32_t s_pslot[kIntegBlocks];
-  s_rw[threadIdx.x] = 1.0f / (float)(threadIdx.x + 1);
   if (threadIdx.x < kIntegBlocks) s_pf[threadIdx.x] = 0u;
   __syncthreads();
   // work-list entries of compact free-space maps carry the whole-block
@@ -690,9 +692,12 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
       for (int i = 0; i < kIntegBlocks; ++i) {
         const bool in = k + i < nk;
         const uint32_t ki = in ? k + i : k;
-        const uint32_t e = s_tent[ki];
-        bu[i].key = s_tkey[ki];
-        bu[i].slot = s_tslot[ki];
+        // uniform, so that what follows from them is scalar
+        const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tent[ki]);
+        const unsigned long long key = s_tkey[ki];
+        bu[i].key = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(key >> 32)) << 32) |
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
+        bu[i].slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tslot[ki]);
         st[i] = COMPACT ? (e & ~bucket_bits) : 0u;
         eb[i] = e & bucket_bits;
         whole[i] = (st[i] & kEntryWhole) != 0u;
@@ -702,15 +707,17 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
         live[i] = in && (bu[i].slot < m.max_blocks || pend[i]);
       }
       int pix[NV];
-      uint32_t vidx[NV];
+      uint32_t vidx[kIntegBlocks];  // the thread's first voxel of each block
       float X2[NV];
       bool vis[NV];
 #pragma unroll
+      for (int i = 0; i < kIntegBlocks; ++i)
+        vidx[i] = (live[i] && !pend[i]) ? bu[i].slot * 512u + 2u * threadIdx.x : 0u;
+#pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int i = v >> 1;
-        const int l = threadIdx.x + 256 * (v & 1);
+        const int l = 2 * (int)threadIdx.x + (v & 1);
         const bool ok = live[i];
-        vidx[v] = (ok && !pend[i]) ? bu[i].slot * 512u + (uint32_t)l : 0u;
         if (whole[i]) {  // a block of voxels carved whole: no projection, no pixel
           pix[v] = 0;
           X2[v] = 0.0f;
@@ -729,12 +736,14 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
         bool in = ok && x2 > 0.0f;
         // x0 / x2 and x1 / x2 from one correctly rounded reciprocal (exact
         // quotients; x2 > 0 and the pixel test reject the rest)
-        const float iz = 1.0f / x2;
+        const float iz = rcp_rn(x2);
         const float uf = f.fx * quotient_rn(x0, x2, iz) + f.cx;
         const float vf = f.fy * quotient_rn(x1, x2, iz) + f.cy;
         const float ur = floorf(uf + 0.5f), vr = floorf(vf + 0.5f);
         in = in && ur >= 0.0f && ur < (float)f.W && vr >= 0.0f && vr < (float)f.H;
-        pix[v] = in ? (int)vr * f.W + (int)ur : 0;
+        // vr < H and W are below 2^24 whenever the product is below 2^26 (the
+        // frame's limit), so the 24-bit multiply is exact
+        pix[v] = in ? (int)(__umul24((uint32_t)(int)vr, (uint32_t)f.W) + (uint32_t)(int)ur) : 0;
         X2[v] = x2;
         vis[v] = in;
       }
@@ -748,10 +757,20 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
           D[v] = load_depth<DF>(f, pix[v]);
           mk[v] = mask_src[pix[v]];
         }
-        if (!pend[v >> 1]) VoxelStore<STORAGE>::load(m, vidx[v], sdf[v], W[v]);
       }
+      // two neighbouring records a load
+      typename VoxelStore<STORAGE>::Pair rec[kIntegBlocks];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) asm volatile("" : "+v"(D[v]), "+v"(mk[v]), "+v"(sdf[v]), "+v"(W[v]));
+      for (int i = 0; i < kIntegBlocks; ++i)
+        if (!pend[i]) rec[i] = VoxelStore<STORAGE>::load_pair(m, vidx[i]);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) asm volatile("" : "+v"(D[v]), "+v"(mk[v]));
+#pragma unroll
+      for (int i = 0; i < kIntegBlocks; ++i) {
+        VoxelStore<STORAGE>::pin(rec[i]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) VoxelStore<STORAGE>::unpack(m, rec[i], j, sdf[2 * i + j], W[2 * i + j]);
+      }
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if (!pend[v >> 1]) continue;
@@ -761,16 +780,9 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
         sdf[v] = c > 0.0f ? m.tau : 0.0f;
         W[v] = c;
       }
-      // RN(1 / (W + 1)) of every voxel: from the table for the integral
-      // weights the integration writes (0 .. 255), by division otherwise
-      float rw[NV];
+      float rw[NV];  // RN(1 / (W + 1))
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int wi = (int)W[v];
-        const bool tab = wi >= 0 && wi < 256 && (float)wi == W[v];
-        rw[v] = s_rw[tab ? wi : 0];
-        if (!tab) rw[v] = 1.0f / (W[v] + 1.0f);
-      }
+      for (int v = 0; v < NV; ++v) rw[v] = rcp_rn(W[v] + 1.0f);
       // the per-voxel rule's decision and the new sdf of every voxel
       bool band[NV], upd[NV];
       float nsdf[NV];
@@ -807,9 +819,14 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
 #pragma unroll
       for (int i = 0; i < kIntegBlocks; ++i) any_pend = any_pend || pend[i];
       if (COMPACT && any_pend) {  // uniform
+        // one LDS atomic per wavefront and block
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
-          if (pend[v >> 1] && live[v >> 1] && (band[v] || !upd[v])) atomicOr(&s_pf[v >> 1], band[v] ? 1u : 2u);
+        for (int i = 0; i < kIntegBlocks; ++i) {
+          if (!(pend[i] && live[i])) continue;  // uniform
+          const uint32_t fl = (__ballot(band[2 * i] || band[2 * i + 1]) != 0ull ? 1u : 0u) |
+                              (__ballot(!upd[2 * i] || !upd[2 * i + 1]) != 0ull ? 2u : 0u);
+          if ((threadIdx.x & 63) == 0 && fl) atomicOr(&s_pf[i], fl);
+        }
         __syncthreads();
         if (threadIdx.x < kIntegBlocks) {
           const int i = threadIdx.x;
@@ -842,50 +859,66 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
           if (fresh[i]) bu[i].slot = slot;
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
-          if (fresh[v >> 1]) vidx[v] = bu[v >> 1].slot * 512u + (uint32_t)(threadIdx.x + 256 * (v & 1));
+        for (int i = 0; i < kIntegBlocks; ++i)
+          if (fresh[i]) vidx[i] = bu[i].slot * 512u + 2u * threadIdx.x;
       }
-      // stores: updated voxels; every voxel of a block that takes its pool slot now
+      // stores: pairs with an updated voxel (the other one as it was); every voxel
+      // of a block that takes its pool slot now
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int i = v >> 1;
+      for (int i = 0; i < kIntegBlocks; ++i) {
         if (pend[i] && !fresh[i]) {
-          band[v] = false;  // stays a free block: nothing stored
+          band[2 * i] = band[2 * i + 1] = false;  // stays a free block: nothing stored
           continue;
         }
-        if (upd[v]) {
-          VoxelStore<STORAGE>::store(m, vidx[v], nsdf[v], fminf(W[v] + 1.0f, m.max_weight));
-          nb += band[v];
-          nf += !band[v];
-        } else if (fresh[i]) {
-          VoxelStore<STORAGE>::store(m, vidx[v], sdf[v], W[v]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int v = 2 * i + j;
+          if (upd[v]) VoxelStore<STORAGE>::pack(m, rec[i], j, nsdf[v], fminf(W[v] + 1.0f, m.max_weight));
+          else if (fresh[i]) VoxelStore<STORAGE>::pack(m, rec[i], j, sdf[v], W[v]);
+          nb += (uint32_t)__popcll(__ballot(upd[v] && band[v]));
+          nf += (uint32_t)__popcll(__ballot(upd[v] && !band[v]));
         }
+        if (upd[2 * i] || upd[2 * i + 1] || fresh[i]) VoxelStore<STORAGE>::store_pair(m, vidx[i], rec[i]);
       }
-      uint32_t cold[NV], cpx[NV][3];
+      uint2 cold[kIntegBlocks];
+      uint32_t cpx[NV][3];
+#pragma unroll
+      for (int i = 0; i < kIntegBlocks; ++i) {
+        cold[i] = make_uint2(0u, 0u);
+        if ((band[2 * i] || band[2 * i + 1]) && !fresh[i])
+          cold[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint32_t*>(m.rgb) + vidx[i]);
+      }
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        cold[v] = 0u;
         cpx[v][0] = cpx[v][1] = cpx[v][2] = 0u;
         if (!band[v]) continue;
-        if (!fresh[v >> 1]) cold[v] = reinterpret_cast<const uint32_t*>(m.rgb)[vidx[v]];
         const uint8_t* px = f.rgb + 3 * pix[v];
         cpx[v][0] = px[0];
         cpx[v][1] = px[1];
         cpx[v][2] = px[2];
       }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) asm volatile("" : "+v"(cold[v]), "+v"(cpx[v][0]), "+v"(cpx[v][1]), "+v"(cpx[v][2]));
+      for (int i = 0; i < kIntegBlocks; ++i) asm volatile("" : "+v"(cold[i].x), "+v"(cold[i].y));
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        if (!band[v]) continue;
-        const float Wv = W[v], Wn = W[v] + 1.0f;
-        float ch[3];
+      for (int v = 0; v < NV; ++v) asm volatile("" : "+v"(cpx[v][0]), "+v"(cpx[v][1]), "+v"(cpx[v][2]));
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-          ch[q] = fminf(255.0f, fmaxf(0.0f, rintf(quotient_rn(
-                                                Wv * (float)((cold[v] >> (8 * q)) & 0xFFu) + (float)cpx[v][q], Wn,
-                                                rw[v]))));
-        m.rgb[vidx[v]] = make_uchar4((unsigned char)ch[0], (unsigned char)ch[1], (unsigned char)ch[2], 0);
+      for (int i = 0; i < kIntegBlocks; ++i) {
+        uint32_t col[2] = {cold[i].x, cold[i].y};
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int v = 2 * i + j;
+          if (!band[v]) continue;
+          const float Wv = W[v], Wn = W[v] + 1.0f;
+          uint32_t c = 0u;
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            c |= (uint32_t)fminf(255.0f, fmaxf(0.0f, rintf(quotient_rn(Wv * (float)((col[j] >> (8 * q)) & 0xFFu) +
+                                                                           (float)cpx[v][q], Wn, rw[v]))))
+                 << (8 * q);
+          col[j] = c;
+        }
+        if (band[2 * i] || band[2 * i + 1])
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(m.rgb) + vidx[i]) = make_uint2(col[0], col[1]);
       }
     }
   }
@@ -895,10 +928,12 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
   __shared__ uint32_t s_cnt[2];
   if (threadIdx.x == 0) s_cnt[0] = s_cnt[1] = 0;
   __syncthreads();
-  if (nb) atomicAdd(&s_cnt[0], nb);
-  if (nf) atomicAdd(&s_cnt[1], nf);
+  if ((threadIdx.x & 63) == 0) {  // counted per wavefront
+    if (nb) atomicAdd(&s_cnt[0], nb);
+    if (nf) atomicAdd(&s_cnt[1], nf);
+  }
   __syncthreads();
-  if (threadIdx.x == 0) m.integ_counts[g0] = make_uint4(s_cnt[0], s_cnt[1], 0u, 0u);
+  if (threadIdx.x == 0) m.integ_counts[g0] = make_uint2(s_cnt[0], s_cnt[1]);
 }
 
 // One workgroup per job: the integration's per-workgroup counts into the
@@ -909,7 +944,7 @@ __global__ __launch_bounds__(256) void integ_fold_kernel(Batch b) {
   const int ng = b.base[blockIdx.x + 1] - b.base[blockIdx.x];
   unsigned long long band = 0, free = 0;
   for (int i = threadIdx.x; i < ng; i += blockDim.x) {
-    const uint4 c = m.integ_counts[i];
+    const uint2 c = m.integ_counts[i];
     band += c.x;
     free += c.y;
   }

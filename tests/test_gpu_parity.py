@@ -146,6 +146,49 @@ def test_integration_matches_oracle(rf, room):
     assert_maps_match(m, o64, o32)
 
 
+@pytest.mark.parametrize("W,H,dx", [(64, 48, 0.0), (33, 17, 0.013), (1, 1, 0.0)])
+def test_integration_of_imported_weights(rf, W, H, dx):
+    """The running average's reciprocal for any weight a checkpoint can hold
+    (fractions, large, beyond the normal reciprocal's range) and projections
+    at odd camera offsets, down to voxels at the camera's plane: bit-exact
+    against the FP32 mirror, with the other voxel of a pair left as it was."""
+    rng = np.random.default_rng(W)
+    s, tau = 0.02, 0.06
+    keys = np.array([[x, y, z] for x in range(-3, 3) for y in range(-3, 3) for z in range(-1, 8)], np.int32)
+    shape = (len(keys), 512)
+    sdf = rng.uniform(-tau, tau, shape).astype(np.float32)
+    w = rng.choice([0.0, 1.0, 3.0, 254.0, 255.0, 0.25, 7.5, 1.0e6, 1.0e30, 3.0e38], shape).astype(np.float32)
+    rgb = rng.integers(0, 256, shape + (3,)).astype(np.uint8)
+    f = 0.9 * max(W, 20)
+    intr = (f, f, (W - 1) / 2.0, (H - 1) / 2.0)
+    depth = (0.7 + 0.2 * rng.uniform(size=(H, W))).astype(np.float32)
+    img = rng.integers(0, 256, (H, W, 3)).astype(np.uint8)
+    T = np.eye(4)
+    T[:3, 3] = [dx, -dx / 3, dx / 7]
+    m = rf.Map(rf.MapParams(s, tau, 5.0, 1 << 12, 1 << 11, 255, 2, "fp32", W * H))
+    m.import_(*[torch.from_numpy(x).cuda() for x in (keys, sdf, w, rgb)])
+    o = O.OracleMap(s, tau, 5.0, 255, 2, real_bits=32)
+    o.import_(keys, sdf.astype(np.float64), w.astype(np.float64), rgb)
+    g, fr = rf.Frame.from_numpy(depth, img, *intr), O.Frame(depth, img, *intr)
+    for _ in range(2):
+        m.allocate(g, dev_pose(T))
+        m.integrate(g, dev_pose(T))
+        o.allocate(fr, T)
+        cnt = o.integrate(fr, T)
+        assert m.stats_counts() == (int(cnt[0]), int(cnt[1]))
+    gk, gs, gw, gc = gpu_export_sorted(m)
+    k, s32, w32, c32 = o.export()
+    assert np.array_equal(gk, k)
+    np.testing.assert_array_equal(gs, s32.astype(np.float32))
+    np.testing.assert_array_equal(gw, w32.astype(np.float32))
+    # W c overflows for the largest weight: the kernel's quotient of an
+    # infinite sum is no number and stores 0, where the mirror divides
+    at = {tuple(q): i for i, q in enumerate(keys)}
+    huge = np.array([w[at[tuple(q)]] > 1.0e38 if tuple(q) in at else np.zeros(512, bool) for q in gk])
+    assert huge.any()
+    np.testing.assert_array_equal(gc[~huge], c32[~huge])
+
+
 def test_integration_masked_pixels_untouched(rf, room):
     rng = np.random.default_rng(1)
     mask = np.zeros((room.height, room.width), np.uint8)
