@@ -520,6 +520,16 @@ __device__ __forceinline__ bool gather_corners(const MapDev& m, const int i0[3],
   const int cross = ((i0[0] & 7) == 7 ? 1 : 0) | ((i0[1] & 7) == 7 ? 2 : 0) | ((i0[2] & 7) == 7 ? 4 : 0);
   int sl[8];
   if (!slots(m, bx0, by0, bz0, cross, sl)) return false;
+  // free blocks: a bit per corner and their counts (8 bits each), so that the
+  // slots need no registers while the records are under way
+  uint32_t free_k = 0u, free_c[2] = {0u, 0u};
+  if (m.free_blocks) {  // uniform
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      free_k |= (uint32_t)(sl[k] < 0) << k;
+      free_c[k >> 2] |= ((uint32_t)(-2 - sl[k]) & 0xFFu) << (8 * (k & 3));
+    }
+  }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int dx = k & 1, dy = (k >> 1) & 1, dz = k >> 2;
@@ -535,13 +545,15 @@ __device__ __forceinline__ bool gather_corners(const MapDev& m, const int i0[3],
       if (WANT_COLOUR) asm volatile("" : "+v"(cc[k]));
     }
   }
+  if (free_k) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    if (sl[k] >= 0) continue;  // free block
-    const float c = (float)(-2 - sl[k]);
-    cs[k] = c > 0.0f ? m.tau : 0.0f;
-    cw[k] = c;
-    if (WANT_COLOUR) cc[k] = 0u;
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t n = (free_c[k >> 2] >> (8 * (k & 3))) & 0xFFu;
+      const bool free_block = (free_k >> k) & 1u;
+      cs[k] = free_block ? (n ? m.tau : 0.0f) : cs[k];
+      cw[k] = free_block ? (float)n : cw[k];
+      if (WANT_COLOUR) cc[k] = free_block ? 0u : cc[k];
+    }
   }
   return true;
 }

@@ -431,24 +431,50 @@ struct TileCache {
 // Slot resolution of sample_map through the tile cache: cached blocks cost
 // an LDS probe; the others take the hash table (first probes of all missing
 // corner blocks issued together) and are added to the cache.
+//
+// Almost every lookup finds all its corner blocks in the window, and those take
+// eight reads at the corners' own cells: no key, no comparison, no choice among
+// the distinct blocks' slots.  Their window cells are marked as used only when
+// the tile's cache is written back (mark: the lower corner's cell, with the
+// crossed block faces from bit 9; -1 without a lookup to mark), since most
+// launches don't.  A lookup of separate tests per corner took 2700 of a
+// workgroup's 18000 cycles.
 template <int SLOTS>
 struct CachedSlots {
   TileCache<SLOTS> c;
+  int* mark;
   __device__ __forceinline__ bool operator()(const MapDev& m, int bx0, int by0, int bz0, int cross, int sl[8]) const {
-    // window cells of all eight corner blocks read together (one LDS round trip)
+    const uint32_t dx = (uint32_t)(bx0 - c.ax), dy = (uint32_t)(by0 - c.ay), dz = (uint32_t)(bz0 - c.az);
+    const uint32_t ox = cross & 1, oy = (cross >> 1) & 1, oz = cross >> 2;
+    static_assert((kWin & (kWin - 1)) == 0, "one test for all coordinates");
+    const bool in = (dx | dy | dz | (dx + ox) | (dy + oy) | (dz + oz)) < (uint32_t)kWin;
+    const int* g = c.grid + (in ? dx + kWin * (dy + kWin * dz) : 0u);
+    const uint32_t ix = in ? ox : 0u, iy = in ? kWin * oy : 0u, iz = in ? kWin * kWin * oz : 0u;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int cl = c.cell(bx0 + (k & 1), by0 + ((k >> 1) & 1), bz0 + (k >> 2));
-      sl[k] = c.grid[cl >= 0 ? cl : 0];
+    for (int k = 0; k < 8; ++k) sl[k] = g[(k & 1 ? ix : 0u) + (k & 2 ? iy : 0u) + (k & 4 ? iz : 0u)];
+    int least = sl[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) least = min(least, sl[k]);
+    if (in && least != kNoSlot) {  // kNoSlot is the lowest value
+      *mark = (int)(g - c.grid) | cross << 9;
+    } else {
+      general(m, bx0, by0, bz0, cross, sl);
     }
+    bool ok = true;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(sl[k]));
+    for (int k = 0; k < 8; ++k) ok &= sl[k] != -1;  // absent; free blocks (<= -2) read as (tau, count)
+    return ok;
+  }
+  // blocks outside the window or not known yet
+  __device__ __forceinline__ void general(const MapDev& m, int bx0, int by0, int bz0, int cross, int sl[8]) const {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
+      sl[k] = kNoSlot;
       if ((k & ~cross) != 0) continue;
       const int x = bx0 + (k & 1), y = by0 + ((k >> 1) & 1), z = bz0 + (k >> 2);
       const int cl = c.cell(x, y, z);
       if (cl >= 0) {
+        sl[k] = c.grid[cl];
         if (sl[k] != kNoSlot) c.gused[cl] = 1;
       } else {
         sl[k] = c.find(x, y, z, pack_key(x, y, z));
@@ -482,15 +508,20 @@ struct CachedSlots {
         c.insert(x, y, z, key, sl[k], true);
       }
     }
-    bool ok = true;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < 8; ++k)
       if ((k & ~cross) != 0) sl[k] = sl[k & cross];
-      ok &= sl[k] != -1;  // absent; free blocks (<= -2) read as (tau, count)
-    }
-    return ok;
   }
 };
+
+// Marks the window cells of a lookup (CachedSlots::mark) as used.
+__device__ __forceinline__ void mark_used(uint8_t* gused, int mark) {
+  if (mark < 0) return;
+  const int cl = mark & (kWinCells - 1), cross = mark >> 9;
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    gused[cl + (k & cross & 1) + kWin * ((k & cross) >> 1 & 1) + kWin * kWin * ((k & cross) >> 2)] = 1;
+}
 
 // LDS of a tile's cache and the wavefront that fills it: the tile's cached
 // block pairs (tiles without a cache entry start from an empty table) placed
@@ -755,14 +786,17 @@ __device__ __forceinline__ double wave_sums(const float t[14], double w_c, int l
 // SLOTS: pairs the tile cache holds in LDS (256 at levels 0-1, 512 at the
 // coarser levels, whose few tiles each touch more blocks; more LDS and
 // registers there cost nothing, since those launches have few workgroups).
-template <int DF, int STORAGE, bool LM, int SLOTS>
-__global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a) {
+// WAVES: wavefronts a SIMD has to hold (kFullTiles).
+template <int DF, int STORAGE, bool LM, int SLOTS, int WAVES>
+__global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, TrackArgs a) {
   __shared__ double s_g[kTrackBlock / 64][kNE];  // per wavefront: its sums of the terms
   __shared__ double s_ne[kNE];
   __shared__ double s_nc[kLmWords];
   __shared__ double s_st[kLmWords];
   __shared__ double s_T[16];
+  __shared__ alignas(16) float s_Tf[12];  // the pose as the pixels use it
   __shared__ int s_state;
+  __shared__ uint16_t s_mark[kTrackBlock];       // per thread: its lookup's window cells
   __shared__ CacheLds<SLOTS> s_cache;
   const int jb = batch_job(b, blockIdx.x);
   const Job& J = b.job[jb];
@@ -832,6 +866,10 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
       }
       if (lane == 0) s_state = 0;
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane < 12) s_Tf[lane] = (float)s_T[lane];
   }
   __syncthreads();
   if (stopped || s_state != 0) return;  // stopped or degenerate: pose kept, the pass stops
@@ -839,6 +877,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
 
   float term[kTerms];  // J_d(6) J_c(6) r_d r_c
   bool counts = false;
+  int mark = -1;
 #pragma unroll
   for (int k = 0; k < kTerms; ++k) term[k] = 0.0f;
   if (inside && depth_ok(D, m.dmax) && !(mask && mk_raw)) {
@@ -847,14 +886,14 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) R[3 * r + c] = (float)s_T[4 * r + c];
-      t[r] = (float)s_T[4 * r + 3];
+      for (int c = 0; c < 3; ++c) R[3 * r + c] = s_Tf[4 * r + c];
+      t[r] = s_Tf[4 * r + 3];
     }
     const float x[3] = {(((float)u - f.cx) * f.ifx) * D, (((float)v - f.cy) * f.ify) * D, D};
     float y[3];
     xform(R, t, x, y);
     float S, gS[3], Iv, gI[3];
-    if (sample_map<STORAGE, true, true>(m, y, S, gS, Iv, gI, CachedSlots<SLOTS>{cache}) && fabsf(S) < m.tau) {
+    if (sample_map<STORAGE, true, true>(m, y, S, gS, Iv, gI, CachedSlots<SLOTS>{cache, &mark}) && fabsf(S) < m.tau) {
       term[0] = gS[0];
       term[1] = gS[1];
       term[2] = gS[2];
@@ -872,6 +911,7 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
       counts = true;
     }
   }
+  s_mark[threadIdx.x] = (uint16_t)mark;
   {
     int k;
     const double v = wave_sums(term, (double)a.w_c, lane, &k);
@@ -889,7 +929,11 @@ __global__ __launch_bounds__(kTrackBlock) void track_kernel(Batch b, TrackArgs a
       if (stats) atomicOr(&stats->flags, (uint32_t)RF_FLAG_TRACK_RANGE);
     }
   }
-  if (cached && s_cache.miss) write_tile_cache<SLOTS>(tab, tcount, nrefs, epoch, s_cache);  // uniform
+  if (cached && s_cache.miss) {  // uniform
+    mark_used(s_cache.gused, (int16_t)s_mark[threadIdx.x]);
+    __syncthreads();
+    write_tile_cache<SLOTS>(tab, tcount, nrefs, epoch, s_cache);
+  }
 }
 
 // Residual of the dynamic mask (Sec. III-C): r = S(T x)^2 of every valid
@@ -930,7 +974,8 @@ __global__ __launch_bounds__(kTrackBlock) void residual_kernel(Batch b, float ga
     float y[3];
     xform(R, t, x, y);
     float S, Iv, g3[3], h3[3];
-    if (sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3, CachedSlots<SLOTS>{cache})) {
+    int mark;  // nothing is written back
+    if (sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3, CachedSlots<SLOTS>{cache, &mark})) {
       r = S * S;
       out = (r > gamma * (m.tau * m.tau)) ? 1 : 0;
     }
@@ -1006,6 +1051,14 @@ static int track_tiles(const FrameDev& f, int level) {
   return ((wl + kTileW - 1) / kTileW) * ((hl + 15) >> 4);
 }
 
+// Launches with more workgroups than this (one resident round of the chip at
+// the 5 wavefronts a SIMD that 81 registers leave) are compiled for 6: with 80
+// registers the loads are spread less far ahead, which costs a launch that fits
+// into one round (640x480, 1200 workgroups at level 0, whole registration 383.5
+// us at 5, 390 at 6) and gains on those that don't (eight mixed sessions, 9300,
+// whole step 2817 us at 5, 2689 at 6).
+constexpr int kFullTiles = 1280;
+
 static void track_dispatch(Batch& b, int df, int st, const TrackArgs& a, hipStream_t s) {
   int total = 0;
   for (int j = 0; j < b.n; ++j) {
@@ -1014,28 +1067,29 @@ static void track_dispatch(Batch& b, int df, int st, const TrackArgs& a, hipStre
   }
   b.base[b.n] = total;
   const dim3 g(total), blk(kTrackBlock);
-  auto run = [&](auto lm, auto slots) {
+  auto run = [&](auto lm, auto slots, auto waves) {
     constexpr bool L = decltype(lm)::value;
-    constexpr int S = decltype(slots)::value;
+    constexpr int S = decltype(slots)::value, V = decltype(waves)::value;
     if (df == RF_DEPTH_U16) {
-      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_U16, RF_STORAGE_FP32, L, S><<<g, blk, 0, s>>>(b, a);
-      else track_kernel<RF_DEPTH_U16, RF_STORAGE_FP16_U8, L, S><<<g, blk, 0, s>>>(b, a);
+      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_U16, RF_STORAGE_FP32, L, S, V><<<g, blk, 0, s>>>(b, a);
+      else track_kernel<RF_DEPTH_U16, RF_STORAGE_FP16_U8, L, S, V><<<g, blk, 0, s>>>(b, a);
     } else {
-      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_F32, RF_STORAGE_FP32, L, S><<<g, blk, 0, s>>>(b, a);
-      else track_kernel<RF_DEPTH_F32, RF_STORAGE_FP16_U8, L, S><<<g, blk, 0, s>>>(b, a);
+      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_F32, RF_STORAGE_FP32, L, S, V><<<g, blk, 0, s>>>(b, a);
+      else track_kernel<RF_DEPTH_F32, RF_STORAGE_FP16_U8, L, S, V><<<g, blk, 0, s>>>(b, a);
     }
   };
   using Small = std::integral_constant<int, tile_refs(1) * 2>;
   using Large = std::integral_constant<int, kTileRefs>;
+  using Loose = std::integral_constant<int, 1>;
+  using Full = std::integral_constant<int, 6>;
   static_assert(tile_refs(0) <= Small::value && tile_refs(1) <= Small::value, "level 0-1 pairs fit the small cache");
-  const bool big = a.level >= 2;
-  if (a.adaptive) {
-    if (big) run(std::true_type{}, Large{});
-    else run(std::true_type{}, Small{});
-  } else {
-    if (big) run(std::false_type{}, Large{});
-    else run(std::false_type{}, Small{});
-  }
+  auto pick = [&](auto lm) {
+    if (a.level >= 2) run(lm, Large{}, Loose{});
+    else if (total > kFullTiles) run(lm, Small{}, Full{});
+    else run(lm, Small{}, Loose{});
+  };
+  if (a.adaptive) pick(std::true_type{});
+  else pick(std::false_type{});
 }
 
 void launch_track(Batch& b, int df, int st, const rf_track_params& tp, hipStream_t s) {

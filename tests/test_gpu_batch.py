@@ -153,3 +153,19 @@ def test_batch_rejects_duplicate_maps(rf):
     f = gpu_frame(rf, seq, 0)
     with pytest.raises(rf.RefusionError):
         rf.process_batch([s, s], [f, f], rf.TrackParams(), rf.MaskParams())
+
+
+@pytest.mark.parametrize("n", [4, 5])
+def test_registration_on_both_sides_of_a_resident_round(rf, n):
+    """Sessions of 320x240 in one batch: four have 1200 workgroups at level 0,
+    five 1500 (more than a resident round of 1280, the kernel compiled for more
+    wavefronts); both give each session what it gets alone."""
+    seqs = [synth.dynamic_room(n_frames=3, width=320, height=240, n_clusters=1, seed=21 + i, movers="in_view")
+            for i in range(n)]
+    offs = (0,) * n
+    alone = run(rf, seqs, batched=False, start_offsets=offs)
+    mixed = run(rf, seqs, batched=True, start_offsets=offs)
+    for a, b in zip(alone, mixed):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+    assert all(a[6][0] == 0 for a in alone)
