@@ -57,14 +57,13 @@ struct TrackArgs {
 __device__ __forceinline__ unsigned long long* acc_buf(const MapDev& m, int b) {
   return reinterpret_cast<unsigned long long*>(m.partials) + (size_t)b * kBufWords;
 }
-// The words an accumulator buffer actually uses: two chunks and a range
-// marker per term per copy (the rest of each 128-byte line is padding against
-// false sharing: atomics on one line are served one after another).
-constexpr int kUsedPerTerm = 3;
-constexpr int kUsedWords = kAccCopies * kNE * kUsedPerTerm;
-__device__ __forceinline__ unsigned long long* used_word(unsigned long long* buf, int q) {
-  const int copy = q / (kNE * kUsedPerTerm), r = q % (kNE * kUsedPerTerm);
-  return buf + copy * kCopyWords + (r / kUsedPerTerm) * kTermWords + (r % kUsedPerTerm);
+// The words an accumulator buffer actually uses: two chunks per term per copy
+// (the rest of each 128-byte line is padding against false sharing: atomics on
+// one line are served one after another).  Entry q of kUsedPairs.
+constexpr int kUsedPairs = kAccCopies * kNE;
+static_assert(kUsedPairs <= kTrackBlock, "a launch clears its share with one store a thread");
+__device__ __forceinline__ ulonglong2* used_pair(unsigned long long* buf, int q) {
+  return reinterpret_cast<ulonglong2*>(buf + (q / kNE) * kCopyWords + (q % kNE) * kTermWords);
 }
 __device__ __forceinline__ double* pose_buf(const MapDev& m, double* user, int b) {
   return b == 2 ? user : reinterpret_cast<double*>(m.partials) + (size_t)3 * kBufWords + 16 * b;
@@ -81,13 +80,14 @@ __device__ __forceinline__ double* lm_state(const MapDev& m, int b) {
 // (one where hi is 0).  The low chunks of a copy sum below 2^63 for up to 2^15
 // workgroups (a 2^26-pixel frame's tiles over the copies), the high chunks of
 // terms below 2^34 likewise.  A non-finite v, or |v| >= 2^34 (beyond that
-// range), is not added: the term's range marker acc[2] is set instead, and
-// its total then reads as NaN, which stops the registration pass
-// (RF_FLAG_TRACK_RANGE).  Returns false in that case.
+// range), is not added: the low chunk's top bit, which its sum does not reach,
+// is set instead, and its total then reads as NaN, which stops the registration
+// pass (RF_FLAG_TRACK_RANGE).  Returns false in that case.
+constexpr unsigned long long kRangeMark = 1ull << 63;
 __device__ __forceinline__ bool fixed_add(unsigned long long* acc, double v) {
   double a = fabs(v) * kFixScale;
   if (!(a < 0x1p94)) {
-    atomicOr(&acc[2], 1ull);
+    atomicOr(&acc[0], kRangeMark);
     return false;
   }
   const double hi_d = floor(a * 0x1p-48);
@@ -102,16 +102,35 @@ __device__ __forceinline__ bool fixed_add(unsigned long long* acc, double v) {
   return true;
 }
 
-// Total of a term over the accumulator copies as FP64 (exact 128-bit integer
-// sum, then conversion).  A term whose range marker is set in any copy
-// totals NaN.
-__device__ __forceinline__ double fixed_total(const unsigned long long* acc) {
+// Totals of the terms over the accumulator copies, by a whole wavefront: lane
+// l of each half reads half of the copies of term l mod 32, a pair of chunks a
+// load, so the 232 lines are asked for by 4 loads (one lane a term took 24
+// loads of a word each, half of a solve's 3000 cycles of waiting for them).
+struct TermLoads {
+  ulonglong2 acc[kAccCopies / 2];
+};
+static_assert(kAccCopies % 2 == 0 && kNE <= 32, "half a wavefront reads half of the copies");
+__device__ __forceinline__ void load_terms(const unsigned long long* buf, int lane, TermLoads& L) {
+  const unsigned long long* p = buf + (lane >> 5) * (kAccCopies / 2 * kCopyWords) + min(lane & 31, kNE - 1) * kTermWords;
+#pragma unroll
+  for (int c = 0; c < kAccCopies / 2; ++c) L.acc[c] = *reinterpret_cast<const ulonglong2*>(p + c * kCopyWords);
+}
+// The value of the lane 32 below or above.
+__device__ __forceinline__ unsigned long long other_half(unsigned long long v) {
+  const bool upper = threadIdx.x & 32;
+  const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+  return ((unsigned long long)(upper ? h[0] : h[1]) << 32) | (upper ? l[0] : l[1]);
+}
+// Total of term lane mod 32 as FP64 (exact 128-bit integer sum, then
+// conversion).  A term whose range mark is set in any copy totals NaN.
+__device__ __forceinline__ double fixed_total(const TermLoads& L) {
   unsigned long long lo = 0, hi = 0, bad = 0;
 #pragma unroll
-  for (int c = 0; c < kAccCopies; ++c) {
-    const unsigned long long s0 = acc[c * kCopyWords];
-    const long long s1 = (long long)acc[c * kCopyWords + 1];
-    bad |= acc[c * kCopyWords + 2];
+  for (int c = 0; c < kAccCopies / 2; ++c) {
+    const unsigned long long s0 = L.acc[c].x & ~kRangeMark;
+    const long long s1 = (long long)L.acc[c].y;
+    bad |= L.acc[c].x;
     // s1 2^48 + s0 as a 128-bit two's complement number, added to (hi, lo)
     const unsigned long long l1 = (unsigned long long)s1 << 48;
     const unsigned long long h1 = (unsigned long long)(s1 >> 16);
@@ -120,7 +139,11 @@ __device__ __forceinline__ double fixed_total(const unsigned long long* acc) {
     lo = n + s0;
     hi += (lo < n ? 1ull : 0ull);
   }
-  if (bad) return __longlong_as_double(0x7FF8000000000000ll);
+  const unsigned long long lo2 = other_half(lo), hi2 = other_half(hi);
+  lo += lo2;
+  hi += hi2 + (lo < lo2 ? 1ull : 0ull);
+  bad |= other_half(bad);
+  if (bad & kRangeMark) return __longlong_as_double(0x7FF8000000000000ll);
   const bool neg = (long long)hi < 0;
   if (neg) {
     lo = ~lo + 1ull;
@@ -130,125 +153,145 @@ __device__ __forceinline__ double fixed_total(const unsigned long long* acc) {
   return neg ? -mag : mag;
 }
 
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+// 1 / x for the magnitudes that pivots have (far from the ends of the range):
+// the hardware's estimate and two Newton steps, half of the division's chain.
+// Equal to the division for each of 4.3e9 random values over 200 powers of two
+// on gfx950.
+__device__ __forceinline__ double rcp_f64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
 }
 
 __device__ __forceinline__ int tri_index(int i, int j) {  // H(i,j), i <= j, packed upper triangle
   return 6 * i - (i * (i - 1)) / 2 + (j - i);
 }
 
-// The solving wavefront of a workgroup: totals -> delta by row-parallel
-// elimination (lane r holds row r of [H + lambda diag H | -g]; no pivoting, H is
-// symmetric positive semi-definite) -> exp(delta^) T.  Writes the new pose
-// (row-major 12 values) to s_T and the outcome to *s_state:
-// 0 ok, RF_FLAG_TRACK_FEW_PIXELS or RF_FLAG_TRACK_SINGULAR (pose kept).
+// The solving wavefront of a workgroup: totals -> delta by elimination of
+// [H + lambda diag H | -g] (no pivoting, H is symmetric positive semi-definite,
+// so its upper triangle is enough) -> exp(delta^) T.  Writes the new pose
+// (row-major 12 values) to s_T, in 32 bits to s_Tf if given, and the outcome to
+// *s_state: 0 ok, RF_FLAG_TRACK_FEW_PIXELS or RF_FLAG_TRACK_SINGULAR (pose kept).
 // A pivot of the elimination equals the squared Cholesky pivot, so the
 // singularity test is the Cholesky one: pivot <= 1e-12 trace(H).
-// tin[0..2] = Tin[ec], Tin[4 + ec], Tin[8 + ec] and tin[3] = Tin[lane] for
-// lanes < 16 (element (er, ec) = (lane / 4, lane % 4) of the input pose).
-__device__ void solve_update_wave(const double* s_ne, const TrackArgs& a, const double tin[4], double* s_T,
-                                  int* s_state) {
+// Tin: the input pose in LDS; lane l < 16 forms element (l / 4, l % 4) of the new one.
+//
+// Every lane solves the whole system: a dependent chain, in which passing rows
+// between lanes costs more than the arithmetic it would save (a row a lane took
+// 96 lane reads and a branch a pivot; with the range test a ballot and the
+// exponential applied as cross products, 3250 -> 2000 cycles from totals to
+// pose).
+__device__ __forceinline__ void solve_update_wave(const double* s_ne, const TrackArgs& a, const double* Tin,
+                                                  double* s_T, float* s_Tf, int* s_state) {
   const int lane = threadIdx.x & 63;
-  int state = 0;
-  bool finite = true;
+  const double own = s_ne[lane < kNE ? lane : 0];
+  double h[21], g[6];
 #pragma unroll
-  for (int k = 0; k < kNE; ++k) finite &= (s_ne[k] == s_ne[k]);
-  if (!finite) state = RF_FLAG_TRACK_RANGE;
-  else if (s_ne[28] < (double)a.min_valid) state = RF_FLAG_TRACK_FEW_PIXELS;
+  for (int k = 0; k < 21; ++k) h[k] = s_ne[k];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) g[i] = -s_ne[21 + i];
   double tr = 0.0;
 #pragma unroll
-  for (int i = 0; i < 6; ++i) tr += s_ne[tri_index(i, i)];
-  const int r = lane < 6 ? lane : 5;
-  double row[7];
+  for (int i = 0; i < 6; ++i) tr += h[tri_index(i, i)];
+  asm volatile("" : "+v"(tr));  // its terms need not outlive the elimination
 #pragma unroll
-  for (int c = 0; c < 6; ++c) row[c] = s_ne[r <= c ? tri_index(r, c) : tri_index(c, r)];
-#pragma unroll
-  for (int c = 0; c < 6; ++c)
-    if (c == r) row[c] *= (1.0 + a.lm_lambda);
-  row[6] = -s_ne[21 + r];
+  for (int i = 0; i < 6; ++i) h[tri_index(i, i)] *= (1.0 + a.lm_lambda);
+  bool singular = false;
   double inv[6];  // reciprocal pivots, reused by the back substitution
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
-    const double piv = readlane_f64(row[k], k);
-    if (!(piv > 1e-12 * tr) && state == 0) state = RF_FLAG_TRACK_SINGULAR;
-    inv[k] = 1.0 / piv;
-    double pk[7];
+    const double piv = h[tri_index(k, k)];
+    singular |= !(piv > 1e-12 * tr);
+    inv[k] = rcp_f64(piv);
 #pragma unroll
-    for (int c = k + 1; c < 7; ++c) pk[c] = readlane_f64(row[c], k);
-    if (lane > k && lane < 6 && state == 0) {
-      const double fct = row[k] * inv[k];
+    for (int i = k + 1; i < 6; ++i) {
+      const double fct = h[tri_index(k, i)] * inv[k];
 #pragma unroll
-      for (int c = k + 1; c < 7; ++c) row[c] = fma(-fct, pk[c], row[c]);
+      for (int c = i; c < 6; ++c) h[tri_index(i, c)] = fma(-fct, h[tri_index(k, c)], h[tri_index(i, c)]);
+      g[i] = fma(-fct, g[k], g[i]);
+      asm volatile("" : "+v"(g[i]));  // or the factors stay in registers until the end
     }
   }
-  double x[6] = {0, 0, 0, 0, 0, 0};
+  double x[6];
+#pragma unroll
+  for (int k = 5; k >= 0; --k) {
+    double s = g[k];
+#pragma unroll
+    for (int j = 5; j > k; --j) s = fma(-h[tri_index(k, j)], x[j], s);
+    x[k] = s * inv[k];
+  }
+  // solved before the branches below, so that the system's registers are free again
+#pragma unroll
+  for (int k = 0; k < 6; ++k) asm volatile("" : "+v"(x[k]));
+  int state = 0;
+  if (__ballot(!(own == own)) != 0ull) state = RF_FLAG_TRACK_RANGE;
+  else if (__ballot(lane == 28 && own < (double)a.min_valid) != 0ull) state = RF_FLAG_TRACK_FEW_PIXELS;
+  else if (__ballot(singular) != 0ull) state = RF_FLAG_TRACK_SINGULAR;
+  const double tin[3] = {Tin[lane & 3], Tin[4 + (lane & 3)], Tin[8 + (lane & 3)]};
+  double out = Tin[lane & 15];
   if (state == 0) {
-#pragma unroll
-    for (int k = 5; k >= 0; --k) {
-      double s = readlane_f64(row[6], k);
-#pragma unroll
-      for (int j = k + 1; j < 6; ++j) s = fma(-readlane_f64(row[j], k), x[j], s);
-      x[k] = s * inv[k];
-    }
-  }
-  if (lane < 16) {
-    double out;
-    if (lane >= 12) {
-      out = (lane == 15) ? 1.0 : 0.0;
-    } else if (state != 0) {
-      out = tin[3];
+    // exp of the twist (rho, phi) = x: R = I + A K + B K^2, t = (I + B K + C K^2) rho
+    // with K v = phi x v, applied to the lane's column of the input pose
+    const double p[3] = {x[3], x[4], x[5]};
+    const double th2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
+    double A, B, C;
+    if (th2 < 1e-2) {
+      // Taylor series of sin(th)/th, (1 - cos th)/th^2, (th - sin th)/th^3 in
+      // th^2 (Horner); for th < 0.1 the first omitted term is below 1e-18
+      A = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 39916800.0, 1.0 / 362880.0), -1.0 / 5040.0),
+                                1.0 / 120.0), -1.0 / 6.0), 1.0);
+      B = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 479001600.0, 1.0 / 3628800.0), -1.0 / 40320.0),
+                                1.0 / 720.0), -1.0 / 24.0), 0.5);
+      C = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 6227020800.0, 1.0 / 39916800.0), -1.0 / 362880.0),
+                                1.0 / 5040.0), -1.0 / 120.0), 1.0 / 6.0);
     } else {
-      // exp of the twist (rho, phi) = x: R = I + A K + B K^2, t = (I + B K + C K^2) rho
-      const double p0 = x[3], p1 = x[4], p2 = x[5];
-      const double th2 = p0 * p0 + p1 * p1 + p2 * p2;
-      double A, B, C;
-      if (th2 < 1e-2) {
-        // Taylor series of sin(th)/th, (1 - cos th)/th^2, (th - sin th)/th^3 in
-        // th^2 (Horner); for th < 0.1 the first omitted term is below 1e-18
-        A = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 39916800.0, 1.0 / 362880.0), -1.0 / 5040.0),
-                                  1.0 / 120.0), -1.0 / 6.0), 1.0);
-        B = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 479001600.0, 1.0 / 3628800.0), -1.0 / 40320.0),
-                                  1.0 / 720.0), -1.0 / 24.0), 0.5);
-        C = fma(th2, fma(th2, fma(th2, fma(th2, fma(th2, -1.0 / 6227020800.0, 1.0 / 39916800.0), -1.0 / 362880.0),
-                                  1.0 / 5040.0), -1.0 / 120.0), 1.0 / 6.0);
-      } else {
-        const double th = sqrt(th2), sn = sin(th), hs = sin(0.5 * th);
-        A = sn / th;
-        B = 2.0 * hs * hs / th2;
-        C = (th - sn) / (th2 * th);
-      }
-      const double ph[3] = {p0, p1, p2};
-      const int er = lane >> 2, ec = lane & 3;
-      // row er of E = exp: E[er][q] for q = 0..2 (rotation) and E[er][3] (translation)
-      double E[4];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        double K = 0.0;  // [phi]x (er, q)
-        if (er == 0 && q == 1) K = -p2;
-        if (er == 0 && q == 2) K = p1;
-        if (er == 1 && q == 0) K = p2;
-        if (er == 1 && q == 2) K = -p0;
-        if (er == 2 && q == 0) K = -p1;
-        if (er == 2 && q == 1) K = p0;
-        const double K2 = ph[er] * ph[q] - (er == q ? th2 : 0.0);
-        E[q] = (er == q ? 1.0 : 0.0) + A * K + B * K2;
-      }
-      {
-        const double rho[3] = {x[0], x[1], x[2]};
-        const double cr[3] = {p1 * rho[2] - p2 * rho[1], p2 * rho[0] - p0 * rho[2], p0 * rho[1] - p1 * rho[0]};
-        const double ccr[3] = {p1 * cr[2] - p2 * cr[1], p2 * cr[0] - p0 * cr[2], p0 * cr[1] - p1 * cr[0]};
-        E[3] = rho[er] + B * cr[er] + C * ccr[er];
-      }
-      out = E[0] * tin[0] + E[1] * tin[1] + E[2] * tin[2];
-      if (ec == 3) out += E[3];
+      const double th = sqrt(th2), sn = sin(th), hs = sin(0.5 * th);
+      A = sn / th;
+      B = 2.0 * hs * hs / th2;
+      C = (th - sn) / (th2 * th);
     }
-    s_T[lane] = out;
+    auto cross = [&](const double v[3], double o[3]) {
+      o[0] = fma(p[1], v[2], -(p[2] * v[1]));
+      o[1] = fma(p[2], v[0], -(p[0] * v[2]));
+      o[2] = fma(p[0], v[1], -(p[1] * v[0]));
+    };
+    double c1[3], c2[3], d1[3], d2[3], o[3];
+    cross(tin, c1);
+    cross(c1, c2);
+    cross(x, d1);  // x[0..2] = rho
+    cross(d1, d2);
+    const bool last = (lane & 3) == 3;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const double t = fma(C, d2[i], fma(B, d1[i], x[i]));
+      o[i] = fma(B, c2[i], fma(A, c1[i], tin[i])) + (last ? t : 0.0);
+    }
+    out = lane < 4 ? o[0] : (lane < 8 ? o[1] : o[2]);
+    if (lane >= 12) out = (lane == 15) ? 1.0 : 0.0;
+  } else if (lane >= 12) {
+    out = (lane == 15) ? 1.0 : 0.0;
   }
+  if (lane < 16) s_T[lane] = out;
+  if (s_Tf && lane < 12) s_Tf[lane] = (float)out;
   if (lane == 0) *s_state = state;
+}
+
+// What the solve reads from memory, asked for before the launch's other loads
+// so that all of it takes one round trip.
+template <bool LM>
+struct SolveLoads {
+  TermLoads terms;
+  double pose;     // element lane mod 16 of the input pose (the candidate's)
+  double st;       // Levenberg-Marquardt state
+  int iters;       // the count that publishing adds to
+};
+template <bool LM>
+__device__ __forceinline__ void solve_loads(const MapDev& m, double* user_pose, const TrackArgs& a,
+                                            const rf_track_stats* stats, int lane, SolveLoads<LM>& L) {
+  load_terms(acc_buf(m, a.acc_read), lane, L.terms);
+  L.pose = pose_buf(m, user_pose, a.pose_read)[lane & 15];
+  if (LM) L.st = lm_state(m, a.state_read)[lane < kLmWords ? lane : 0];
+  L.iters = stats ? stats->iters : 0;
 }
 
 // The solve step shared by the tracking and finalize launches, run by the
@@ -265,43 +308,30 @@ __device__ void solve_update_wave(const double* s_ne, const TrackArgs& a, const 
 // final_only (the last decision of a pass) no step follows and the accepted
 // pose is the result.  s_nc, s_st: LDS scratch of kLmWords doubles each.
 template <bool LM>
-__device__ void solve_step(const MapDev& m, double* user_pose, const TrackArgs& a, rf_track_stats* stats,
-                           double* s_ne, double* s_T, int* s_state, bool publish, bool stopped, bool final_only,
-                           double* s_nc, double* s_st) {
+__device__ __forceinline__ void solve_step(const MapDev& m, double* user_pose, const TrackArgs& a,
+                                           rf_track_stats* stats, SolveLoads<LM>& L, double* s_ne, double* s_T,
+                                           float* s_Tf, int* s_state, bool publish, bool stopped, bool final_only,
+                                           double* s_nc, double* s_st) {
   const int lane = threadIdx.x & 63;
-  const int ec = lane & 3;
-  // the input pose is fetched together with the totals (one round trip)
-  double tin[4] = {0.0, 0.0, 0.0, 0.0};
+  const double* Tin = s_nc + kNE;
   double lam = a.lm_lambda;
   bool accept = true, first = true;
+#pragma unroll
+  for (int c = 0; c < kAccCopies / 2; ++c) asm volatile("" : "+v"(L.terms.acc[c].x), "+v"(L.terms.acc[c].y));
+  asm volatile("" : "+v"(L.pose), "+v"(L.iters));
+  const double tot = fixed_total(L.terms);
   if (!LM) {
-    // pose and totals are loaded without branches (clamped lanes) so all the
-    // loads share one round trip; the pose goes through LDS (fewer registers
-    // held across the solve)
-    double pin = pose_buf(m, user_pose, a.pose_read)[lane < 16 ? lane : 0];
-    const double tot = fixed_total(acc_buf(m, a.acc_read) + (lane < kNE ? lane : 0) * kTermWords);
-    asm volatile("" : "+v"(pin));
-    if (lane < 16) s_nc[kNE + lane] = pin;
+    // the pose goes through LDS (fewer registers held across the solve)
+    if (lane < 16) s_nc[kNE + lane] = L.pose;
     if (lane < kNE) s_ne[lane] = tot;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < 16) {
-      tin[0] = s_nc[kNE + ec];
-      tin[1] = s_nc[kNE + 4 + ec];
-      tin[2] = s_nc[kNE + 8 + ec];
-      tin[3] = s_nc[kNE + lane];
-    }
   } else {
-    const double* C = pose_buf(m, user_pose, a.pose_read);  // the candidate just evaluated
-    const double* S = lm_state(m, a.state_read);
-    double cin = C[lane < 16 ? lane : 0];
-    double st_in = S[lane < kLmWords ? lane : 0];
-    const double tot = fixed_total(acc_buf(m, a.acc_read) + (lane < kNE ? lane : 0) * kTermWords);
-    asm volatile("" : "+v"(cin), "+v"(st_in));
+    asm volatile("" : "+v"(L.st));
     if (lane < kNE) s_nc[lane] = tot;
-    if (lane < kLmWords) s_st[lane] = st_in;
-    if (lane < 16) s_nc[kNE + lane] = cin;
+    if (lane < kLmWords) s_st[lane] = L.st;
+    if (lane < 16) s_nc[kNE + lane] = L.pose;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -310,24 +340,18 @@ __device__ void solve_step(const MapDev& m, double* user_pose, const TrackArgs& 
     lam = s_st[45];
     if (!first) lam = accept ? lam / 10.0 : fmax(lam * 10.0, 1e-4);
     if (lane < kNE) s_ne[lane] = accept ? s_nc[lane] : s_st[16 + lane];
-    if (lane < 16) {
-      const double* Ta = accept ? s_nc + kNE : s_st;
-      tin[0] = Ta[ec];
-      tin[1] = Ta[4 + ec];
-      tin[2] = Ta[8 + ec];
-      tin[3] = Ta[lane];
-    }
+    if (!accept) Tin = s_st;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (final_only) {
-    if (lane < 16) s_T[lane] = tin[3];
+    if (lane < 16) s_T[lane] = Tin[lane];
     if (lane == 0) *s_state = 0;
   } else {
     TrackArgs ta = a;
     ta.lm_lambda = lam;
-    solve_update_wave(s_ne, ta, tin, s_T, s_state);
+    solve_update_wave(s_ne, ta, Tin, s_T, s_Tf, s_state);
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -341,7 +365,7 @@ __device__ void solve_step(const MapDev& m, double* user_pose, const TrackArgs& 
   }
   if (LM && a.state_write >= 0) {
     double* S = lm_state(m, a.state_write);
-    if (lane < 16) S[lane] = tin[3];
+    if (lane < 16) S[lane] = Tin[lane];
     if (lane < kNE) S[16 + lane] = s_ne[lane];
     if (lane == 0) S[45] = lam;
   }
@@ -352,7 +376,7 @@ __device__ void solve_step(const MapDev& m, double* user_pose, const TrackArgs& 
       if (a.prev_first && a.prev_level >= 0 && a.prev_level < 8)
         stats->level_count[a.prev_level] = LM ? s_nc[28] : s_ne[28];
       if (state != 0) stats->flags |= (uint32_t)state;
-      else if (LM ? (accept && !first) : !final_only) stats->iters += 1;
+      else if (LM ? (accept && !first) : !final_only) stats->iters = L.iters + 1;
     }
     if (state != 0) {
       m.st->track_stop = 1;
@@ -786,9 +810,18 @@ __device__ __forceinline__ double wave_sums(const float t[14], double w_c, int l
 // SLOTS: pairs the tile cache holds in LDS (256 at levels 0-1, 512 at the
 // coarser levels, whose few tiles each touch more blocks; more LDS and
 // registers there cost nothing, since those launches have few workgroups).
-// WAVES: wavefronts a SIMD has to hold (kFullTiles).
-template <int DF, int STORAGE, bool LM, int SLOTS, int WAVES>
-__global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, TrackArgs a) {
+// SOLVE: the launch solves the previous evaluation's system at its start if asked
+// to (kSeparateSolveTiles); one that never does keeps 6 wavefronts a SIMD.
+// ONE: a batch of one job, whose arguments are then asked for at once instead
+// of after the search for the workgroup's job.
+//
+// What bounds a launch of few workgroups is its chain: arguments, totals, solve,
+// corner slots, corner records, sums, atomics.  With the totals asked for
+// before the pixels, the solve by every lane and single-job arguments a
+// registration of 160x120 (20 launches) takes 152 us instead of 184, of 640x480
+// (30) 330 instead of 383.
+template <int DF, int STORAGE, bool LM, int SLOTS, bool SOLVE, bool ONE>
+__global__ __launch_bounds__(kTrackBlock, SOLVE ? 5 : 6) void track_kernel(Batch b, TrackArgs a) {
   __shared__ double s_g[kTrackBlock / 64][kNE];  // per wavefront: its sums of the terms
   __shared__ double s_ne[kNE];
   __shared__ double s_nc[kLmWords];
@@ -798,14 +831,21 @@ __global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, Trac
   __shared__ int s_state;
   __shared__ uint16_t s_mark[kTrackBlock];       // per thread: its lookup's window cells
   __shared__ CacheLds<SLOTS> s_cache;
-  const int jb = batch_job(b, blockIdx.x);
+  const int jb = ONE ? 0 : batch_job(b, blockIdx.x);
   const Job& J = b.job[jb];
   const MapDev& m = J.m;
   const FrameDev& f = J.f;
   const uint8_t* mask = J.mask;
   double* user_pose = J.pose;
   rf_track_stats* stats = J.stats;
-  const int g0 = blockIdx.x - b.base[jb];  // tile index within the job
+  const int g0 = ONE ? (int)blockIdx.x : (int)blockIdx.x - b.base[jb];  // tile index within the job
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // the solving wavefront (and the cache builder after it) rotate with the
+  // tile index, so the solves of the workgroups sharing a CU spread over its
+  // SIMDs
+  const int sw = g0 & 3, cw = (sw + 1) & 3;
+  SolveLoads<LM> solve_in;
+  if (SOLVE && wave == sw && a.solve) solve_loads<LM>(m, user_pose, a, stats, lane, solve_in);
   // Set only by earlier launches.  Read here but acted on after the pixel
   // loads and the solve are under way: only publishing waits for it.
   const uint32_t stopped = m.st->track_stop;
@@ -816,7 +856,6 @@ __global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, Trac
   const int lv = a.level;
   const int wl = (f.W + (1 << lv) - 1) >> lv;
   const int hl = (f.H + (1 << lv) - 1) >> lv;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int tiles_x = (wl + kTileW - 1) / kTileW;
   const int ul = (g0 % tiles_x) * kTileW + (wave % (kTileW / 8)) * 8 + (lane & 7);
   const int vl = (g0 / tiles_x) * 16 + (wave / (kTileW / 8)) * 8 + (lane >> 3);
@@ -831,11 +870,9 @@ __global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, Trac
   const uint8_t* px = f.rgb + 3 * pix;
   const uint8_t c0 = px[0], c1 = px[1], c2 = px[2];
   if (a.acc_clear >= 0) {
-    // the workgroups of the job share the clearing of the used chunk words
-    const int ng = b.base[jb + 1] - b.base[jb];
-    const int per = (kUsedWords + ng - 1) / ng;
-    const int q1 = min(g0 * per + per, kUsedWords);
-    for (int q = g0 * per + threadIdx.x; q < q1; q += kTrackBlock) *used_word(acc_buf(m, a.acc_clear), q) = 0ull;
+    // the workgroups of the job share the clearing of the used chunk pairs
+    const int q = g0 + (int)threadIdx.x * (b.base[jb + 1] - b.base[jb]);
+    if (q < kUsedPairs) *used_pair(acc_buf(m, a.acc_clear), q) = make_ulonglong2(0ull, 0ull);
   }
   // the tile's cached block pairs (the wavefront after the solving one,
   // while it solves); tiles without a cache entry start from an empty table
@@ -844,18 +881,14 @@ __global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, Trac
                   (size_t)(cached ? g0 : 0) * tile_refs(cached ? a.level : 0);
   uint32_t* tcount = m.tc_count + (size_t)(cached ? a.level : 0) * m.tc_tiles + (cached ? g0 : 0);
   const int nrefs = tile_refs(a.level);
-  // the solving wavefront (and the cache builder after it) rotate with the
-  // tile index, so the solves of the workgroups sharing a CU spread over its
-  // SIMDs
-  const int sw = g0 & 3, cw = (sw + 1) & 3;
   if (wave == cw) build_tile_cache<SLOTS>(tab, tcount, cached, nrefs, epoch, lane, s_cache);
   if (wave == sw) {
-    if (a.solve) {
-      solve_step<LM>(m, user_pose, a, stats, s_ne, s_T, &s_state, g0 == 0, stopped != 0, false, s_nc, s_st);
+    if (SOLVE && a.solve) {
+      solve_step<LM>(m, user_pose, a, stats, solve_in, s_ne, s_T, s_Tf, &s_state, g0 == 0, stopped != 0, false, s_nc, s_st);
     } else {
       const double* Tin = pose_buf(m, user_pose, a.pose_read);
       if (lane < 16) {
-        s_T[lane] = Tin[lane];
+        if (lane < 12) s_Tf[lane] = (float)Tin[lane];
         if (g0 == 0 && !stopped && a.pose_write >= 0) pose_buf(m, user_pose, a.pose_write)[lane] = Tin[lane];
       }
       if (LM && g0 == 0 && !stopped && a.state_write >= 0) {
@@ -866,10 +899,6 @@ __global__ __launch_bounds__(kTrackBlock, WAVES) void track_kernel(Batch b, Trac
       }
       if (lane == 0) s_state = 0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < 12) s_Tf[lane] = (float)s_T[lane];
   }
   __syncthreads();
   if (stopped || s_state != 0) return;  // stopped or degenerate: pose kept, the pass stops
@@ -999,7 +1028,10 @@ __global__ __launch_bounds__(64) void track_finalize_kernel(Batch b, TrackArgs a
   const MapDev& m = J.m;
   double* user_pose = J.pose;
   if (a.mode == 1) {
-    if (threadIdx.x < kNE) out29[threadIdx.x] = fixed_total(acc_buf(m, a.acc_read) + threadIdx.x * kTermWords);
+    TermLoads L;
+    load_terms(acc_buf(m, a.acc_read), threadIdx.x, L);
+    const double tot = fixed_total(L);
+    if (threadIdx.x < kNE) out29[threadIdx.x] = tot;
     return;
   }
   if (m.st->track_stop) {
@@ -1007,21 +1039,23 @@ __global__ __launch_bounds__(64) void track_finalize_kernel(Batch b, TrackArgs a
     if (a.mode == 0 && threadIdx.x < 16) user_pose[threadIdx.x] = pose_buf(m, user_pose, a.pose_read)[threadIdx.x];
     return;
   }
-  if (a.mode == 2) {
-    // the solve a tracking launch would run at its start, once per job
-    if (a.adaptive) solve_step<true>(m, user_pose, a, J.stats, s_ne, s_T, &s_state, true, false, false, s_nc, s_st);
-    else solve_step<false>(m, user_pose, a, J.stats, s_ne, s_T, &s_state, true, false, false, s_nc, s_st);
-    return;
-  }
-  if (a.adaptive) solve_step<true>(m, user_pose, a, J.stats, s_ne, s_T, &s_state, true, false, true, s_nc, s_st);
-  else solve_step<false>(m, user_pose, a, J.stats, s_ne, s_T, &s_state, true, false, false, s_nc, s_st);
+  // mode 2: the solve a tracking launch would run at its start, once per job
+  const bool final_only = a.mode != 2;
+  auto solve = [&](auto lm) {
+    constexpr bool LM = decltype(lm)::value;
+    SolveLoads<LM> L;
+    solve_loads<LM>(m, user_pose, a, J.stats, threadIdx.x, L);
+    solve_step<LM>(m, user_pose, a, J.stats, L, s_ne, s_T, nullptr, &s_state, true, false, LM && final_only, s_nc, s_st);
+  };
+  if (a.adaptive) solve(std::true_type{});
+  else solve(std::false_type{});
 }
 
 __global__ void track_reset_kernel(Batch b) {
   const Job& J = b.job[blockIdx.x];
   for (int bi = 0; bi < 3; ++bi) {
     unsigned long long* acc = acc_buf(J.m, bi);
-    for (int q = threadIdx.x; q < kUsedWords; q += blockDim.x) *used_word(acc, q) = 0ull;
+    for (int q = threadIdx.x; q < kUsedPairs; q += blockDim.x) *used_pair(acc, q) = make_ulonglong2(0ull, 0ull);
   }
   if (threadIdx.x == 0) {
     J.m.st->track_stop = 0;
@@ -1043,6 +1077,9 @@ __global__ void track_reset_kernel(Batch b) {
 // many workgroups the redundant solves and the reads of the accumulator
 // copies they share cost more than the extra launch.  Both schedules run the
 // same solve on the same totals, so the poses are identical.
+// Eight mixed sessions, a whole step: 2575 us with this line, 2636 at 1280 (one
+// resident round).  The evaluation that then never solves is compiled without
+// the solve: 80 registers, 6 wavefronts a SIMD.
 constexpr int kSeparateSolveTiles = 3072;
 
 static int track_tiles(const FrameDev& f, int level) {
@@ -1050,14 +1087,6 @@ static int track_tiles(const FrameDev& f, int level) {
   const int hl = (f.H + (1 << level) - 1) >> level;
   return ((wl + kTileW - 1) / kTileW) * ((hl + 15) >> 4);
 }
-
-// Launches with more workgroups than this (one resident round of the chip at
-// the 5 wavefronts a SIMD that 81 registers leave) are compiled for 6: with 80
-// registers the loads are spread less far ahead, which costs a launch that fits
-// into one round (640x480, 1200 workgroups at level 0, whole registration 383.5
-// us at 5, 390 at 6) and gains on those that don't (eight mixed sessions, 9300,
-// whole step 2817 us at 5, 2689 at 6).
-constexpr int kFullTiles = 1280;
 
 static void track_dispatch(Batch& b, int df, int st, const TrackArgs& a, hipStream_t s) {
   int total = 0;
@@ -1067,26 +1096,30 @@ static void track_dispatch(Batch& b, int df, int st, const TrackArgs& a, hipStre
   }
   b.base[b.n] = total;
   const dim3 g(total), blk(kTrackBlock);
-  auto run = [&](auto lm, auto slots, auto waves) {
+  auto run = [&](auto lm, auto slots, auto solve, auto one) {
     constexpr bool L = decltype(lm)::value;
-    constexpr int S = decltype(slots)::value, V = decltype(waves)::value;
+    constexpr int S = decltype(slots)::value;
+    constexpr bool V = decltype(solve)::value;
+    constexpr bool O = decltype(one)::value;
     if (df == RF_DEPTH_U16) {
-      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_U16, RF_STORAGE_FP32, L, S, V><<<g, blk, 0, s>>>(b, a);
-      else track_kernel<RF_DEPTH_U16, RF_STORAGE_FP16_U8, L, S, V><<<g, blk, 0, s>>>(b, a);
+      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_U16, RF_STORAGE_FP32, L, S, V, O><<<g, blk, 0, s>>>(b, a);
+      else track_kernel<RF_DEPTH_U16, RF_STORAGE_FP16_U8, L, S, V, O><<<g, blk, 0, s>>>(b, a);
     } else {
-      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_F32, RF_STORAGE_FP32, L, S, V><<<g, blk, 0, s>>>(b, a);
-      else track_kernel<RF_DEPTH_F32, RF_STORAGE_FP16_U8, L, S, V><<<g, blk, 0, s>>>(b, a);
+      if (st == RF_STORAGE_FP32) track_kernel<RF_DEPTH_F32, RF_STORAGE_FP32, L, S, V, O><<<g, blk, 0, s>>>(b, a);
+      else track_kernel<RF_DEPTH_F32, RF_STORAGE_FP16_U8, L, S, V, O><<<g, blk, 0, s>>>(b, a);
     }
   };
   using Small = std::integral_constant<int, tile_refs(1) * 2>;
   using Large = std::integral_constant<int, kTileRefs>;
-  using Loose = std::integral_constant<int, 1>;
-  using Full = std::integral_constant<int, 6>;
+  using Solve = std::true_type;
+  using Apart = std::false_type;
   static_assert(tile_refs(0) <= Small::value && tile_refs(1) <= Small::value, "level 0-1 pairs fit the small cache");
   auto pick = [&](auto lm) {
-    if (a.level >= 2) run(lm, Large{}, Loose{});
-    else if (total > kFullTiles) run(lm, Small{}, Full{});
-    else run(lm, Small{}, Loose{});
+    using One = std::true_type;
+    using Many = std::false_type;
+    if (a.level >= 2) b.n == 1 ? run(lm, Large{}, Solve{}, One{}) : run(lm, Large{}, Solve{}, Many{});
+    else if (!a.solve) run(lm, Small{}, Apart{}, Many{});
+    else b.n == 1 ? run(lm, Small{}, Solve{}, One{}) : run(lm, Small{}, Solve{}, Many{});
   };
   if (a.adaptive) pick(std::true_type{});
   else pick(std::false_type{});
