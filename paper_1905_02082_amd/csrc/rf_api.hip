@@ -281,7 +281,7 @@ rf_status hashmap_create(const rf_map_params* p, void* arena, size_t bytes, void
   d.dmax = p->depth_max;
   d.max_weight = (float)p->max_weight;
   d.carve_stride = p->carve_stride;
-  rf::launch_map_init(d, p->num_buckets, p->storage, S(stream));
+  rf::launch_map_init(d, p->num_buckets, p->storage, true, S(stream));
   st = check_launch("hashmap_create");
   if (st) {
     delete m;
@@ -298,7 +298,7 @@ rf_status hashmap_destroy(rf_map* m) {
 
 rf_status hashmap_reset(rf_map* m, void* stream) {
   if (!m) return fail(RF_EINVAL, "map is NULL");
-  rf::launch_map_init(m->h.dev, m->h.p.num_buckets, m->h.p.storage, S(stream));
+  rf::launch_map_init(m->h.dev, m->h.p.num_buckets, m->h.p.storage, false, S(stream));
   return check_launch("hashmap_reset");
 }
 

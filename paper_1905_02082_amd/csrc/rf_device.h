@@ -106,6 +106,7 @@ struct DevState {
   unsigned long long cum_whole;   // since create/reset: listed blocks carved whole (compact free space)
   uint32_t w_count;        // compact free space: entries in wlist
   uint32_t n_whole;        // compact free space: listed blocks carved whole by the running integration
+  uint32_t mark;           // map_mark once initialised: n_blocks tells which pool slots were ever used
 };
 
 // Starts a new allocation epoch (the tag of the tracking caches' entries for

@@ -73,7 +73,8 @@ size_t flood_member_bytes(const FrameDev& f);  // 1 bit a pixel
 // residual and raw decision of the mask (its first stage), through the tracking tile cache
 void launch_residual(Batch& b, int depth_format, int storage, float gamma, hipStream_t s);
 
-void launch_map_init(const MapDev& m, uint32_t num_buckets, int storage, hipStream_t s);
+// whole: a new arena (nothing is known of its contents)
+void launch_map_init(const MapDev& m, uint32_t num_buckets, int storage, bool whole, hipStream_t s);
 void launch_surface(const MapDev& m, int storage, float* pts, uint32_t cap, uint32_t* count, hipStream_t s);
 void launch_mesh(const MapDev& m, int storage, float* tris, uint32_t cap, uint32_t* count, hipStream_t s);
 void launch_raycast(const MapDev& m, const FrameDev& f, int depth_format, int storage, const double* pose,
