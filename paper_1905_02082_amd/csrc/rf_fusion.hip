@@ -397,8 +397,14 @@ __global__ __launch_bounds__(256, 6) void alloc_kernel(Batch b) {
 // the order of the list is not fixed, its content is), the marks cleared on
 // the way.  One workgroup per CU and job streams a contiguous range of the
 // byte map, 16 buckets per load.
+//
+// A workgroup's chain bounds it: its part of the map, kListLoads loads a
+// thread asked for together, positions by ballots of the counts' bits, one
+// counter atomic, the entries.  With a load, a prefix by shuffles and an LDS
+// atomic in turn for each 256 chunks: 10.5 us for 2^22 buckets, 7.5 now.
 constexpr int kListGroups = 256;   // workgroups of the listing (all jobs together)
 constexpr uint32_t kListRun = 2048;
+constexpr int kListLoads = 4;
 
 __global__ __launch_bounds__(256) void list_frame_kernel(Batch b) {
   __shared__ uint32_t s_run[kListRun];
@@ -409,37 +415,44 @@ __global__ __launch_bounds__(256) void list_frame_kernel(Batch b) {
   const uint32_t g0 = blockIdx.x - b.base[jb], gn = b.base[jb + 1] - b.base[jb];
   const uint32_t per = (nc + gn - 1) / gn;
   const uint32_t c0 = g0 * per, c1 = min(c0 + per, nc);
+  const int lane = threadIdx.x & 63;
   uint4* map = reinterpret_cast<uint4*>(touched_map(m));
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
-  for (uint32_t cb = c0; cb < c1; cb += blockDim.x) {  // uniform
-    const uint32_t c = cb + threadIdx.x;
-    const uint4 w = c < c1 ? map[c] : make_uint4(0u, 0u, 0u, 0u);
-    const uint32_t words[4] = {w.x, w.y, w.z, w.w};
-    uint32_t cnt = 0;
+  for (uint32_t cb = c0; cb < c1; cb += kListLoads * blockDim.x) {  // uniform
+    uint4 w[kListLoads];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) cnt += __popc(words[k] & 0x01010101u);
-    if (cnt) map[c] = make_uint4(0u, 0u, 0u, 0u);
-    // positions in the workgroup's run: a prefix over the wavefront's counts
-    // (shuffles), one LDS atomic per wavefront
-    uint32_t pre = cnt;
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = __shfl_up(pre, o);
-      if (lane >= o) pre += t;
+    for (int q = 0; q < kListLoads; ++q) {
+      const uint32_t c = cb + q * blockDim.x + threadIdx.x;
+      w[q] = map[min(c, nc - 1u)];
     }
-    const uint32_t total = __shfl(pre, 63);
-    uint32_t base = 0;
-    if (total && lane == 63) base = atomicAdd(&s_n, total);  // LDS
-    base = __shfl(base, 63);
-    uint32_t i = base + pre - cnt;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int q = 0; q < kListLoads; ++q) asm volatile("" : "+v"(w[q].x), "+v"(w[q].y), "+v"(w[q].z), "+v"(w[q].w));
 #pragma unroll
-      for (int by = 0; by < 4; ++by) {
-        if (!((words[k] >> (8 * by)) & 1u)) continue;
-        const uint32_t h = c * 16u + 4u * k + by;
+    for (int q = 0; q < kListLoads; ++q) {
+      const uint32_t c = cb + q * blockDim.x + threadIdx.x;
+      const uint32_t words[4] = {w[q].x, w[q].y, w[q].z, w[q].w};
+      uint32_t marks = 0;  // a bit per bucket
+#pragma unroll
+      for (int k = 0; k < 4; ++k) marks |= (((words[k] & 0x01010101u) * 0x01020408u) >> 24 & 15u) << (4 * k);
+      if (c >= c1) marks = 0;
+      const uint32_t cnt = __popc(marks);
+      if (__ballot(cnt != 0) == 0ull) continue;  // uniform
+      if (cnt) map[c] = make_uint4(0u, 0u, 0u, 0u);
+      // positions in the workgroup's run: the lanes before and in all, a bit of
+      // the counts (at most 16) at a time, and one LDS atomic per wavefront
+      uint32_t pre = 0, total = 0;
+#pragma unroll
+      for (int bit = 0; bit < 5; ++bit) {
+        const unsigned long long set = __ballot((cnt >> bit) & 1u);
+        pre += __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u)) << bit;
+        total += (uint32_t)__popcll(set) << bit;
+      }
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&s_n, total);  // LDS
+      uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + pre;
+      for (; marks; marks &= marks - 1u, ++i) {
+        const uint32_t h = c * 16u + (uint32_t)__ffs((int)marks) - 1u;
         if (i < kListRun) {
           s_run[i] = h;
         } else {
@@ -447,7 +460,6 @@ __global__ __launch_bounds__(256) void list_frame_kernel(Batch b) {
           const uint32_t kk = atomicAdd(&m.st->f_count, 1u);
           if (kk < m.flist_cap) m.flist[kk] = h;
         }
-        ++i;
       }
     }
   }
