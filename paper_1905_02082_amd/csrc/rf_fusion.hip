@@ -503,6 +503,7 @@ constexpr uint32_t kEntryFresh = 0x40000000u;  // a free block (alone: not carve
 constexpr int kEntryCountShift = 22;           // the free block's count (bits 22-29)
 constexpr float kCarveMargin = 1.0e-3f;        // metres
 constexpr int kMaxTestCells = 64;
+constexpr int kCellLoads = 8;  // 4: 13.9 us, 8 and 16: 12
 constexpr int kClassifyGroups = 512;           // workgroups of the whole-block test (all jobs together)
 
 // One wavefront per 8x8 cell (lane = pixel), four cells per workgroup.  The
@@ -563,10 +564,30 @@ __device__ __forceinline__ bool carved_whole(const MapDev& m, const FrameDev& f,
   if (!(u0 >= 0.0f && v0 >= 0.0f && u1 <= (float)(f.W - 1) && v1 <= (float)(f.H - 1))) return false;
   const int c0 = (int)u0 / kCell, c1 = (int)u1 / kCell, r0 = (int)v0 / kCell, r1 = (int)v1 / kCell;
   if ((c1 - c0 + 1) * (r1 - r0 + 1) > kMaxTestCells) return false;
-  float dmin = INFINITY;
-  for (int r = r0; r <= r1; ++r)
-    for (int c = c0; c <= c1; ++c) dmin = fminf(dmin, m.cells[r * J.cells_w + c]);
-  return dmin > zmax + m.tau + kCarveMargin;
+  // the rectangle's cells line by line, kCellLoads a round trip (the last one
+  // again past the end), until one is too near: asked for one by one, up to 64
+  // in a row, the kernel took 17 us instead of 12 (1280x720)
+  const float need = zmax + m.tau + kCarveMargin;
+  const int n = (c1 - c0 + 1) * (r1 - r0 + 1), skip = J.cells_w - (c1 - c0 + 1);
+  int at = r0 * J.cells_w + c0, c = c0;
+  bool far = true;
+  for (int i = 0; i < n && far; i += kCellLoads) {
+    float d[kCellLoads];
+#pragma unroll
+    for (int k = 0; k < kCellLoads; ++k) {
+      d[k] = m.cells[at];
+      if (i + k + 1 < n) {
+        const bool wrap = c == c1;
+        at += wrap ? skip + 1 : 1;
+        c = wrap ? c0 : c + 1;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kCellLoads; ++k) asm volatile("" : "+v"(d[k]));
+#pragma unroll
+    for (int k = 0; k < kCellLoads; ++k) far = far && d[k] > need;
+  }
+  return far;
 }
 
 __global__ __launch_bounds__(256) void classify_kernel(Batch b) {
@@ -622,7 +643,8 @@ __global__ __launch_bounds__(256) void classify_kernel(Batch b) {
   __shared__ uint32_t s_whole;
   if (threadIdx.x == 0) s_whole = 0;
   __syncthreads();
-  if (n_whole) atomicAdd(&s_whole, n_whole);
+  for (int o = 32; o > 0; o >>= 1) n_whole += __shfl_xor(n_whole, o);
+  if (lane == 0 && n_whole) atomicAdd(&s_whole, n_whole);
   __syncthreads();
   if (threadIdx.x == 0 && s_whole) atomicAdd(&m.st->n_whole, s_whole);
 }

@@ -183,27 +183,61 @@ void launch_surface(const MapDev& m, int storage, float* pts, uint32_t cap, uint
 }
 
 // Free blocks of a compact free-space map: key and the weight their voxels
-// read as, in no particular order (the buckets are scanned).
+// read as, in no particular order (the buckets are scanned).  A workgroup takes
+// kFreeScan buckets a thread at a time, all asked for together, and one atomic
+// for the room of what it found: an atomic a wavefront and 64 buckets, all on
+// one counter, took 54 us for 2^20 buckets, this 9.
+constexpr int kFreeScan = 8;
+
 __global__ __launch_bounds__(256) void export_free_kernel(MapDev m, uint32_t num_buckets, int32_t* keys, float* w,
                                                           uint32_t cap, uint32_t* count) {
-  for (uint32_t h = blockIdx.x * blockDim.x + threadIdx.x; h < num_buckets; h += gridDim.x * blockDim.x) {
-    const Bucket b = m.buckets[h];
-    if (b.key == kEmptyKey || !is_free_slot(b.slot)) continue;
-    const uint32_t i = atomicAdd(count, 1u);
-    if (i >= cap) continue;
-    int x, y, z;
-    unpack_key(b.key, x, y, z);
-    keys[3 * i] = x;
-    keys[3 * i + 1] = y;
-    keys[3 * i + 2] = z;
-    if (w) w[i] = (float)(b.slot & 0xFFu);
+  __shared__ uint32_t s_n, s_base;
+  const int lane = threadIdx.x & 63;
+  for (uint32_t h0 = blockIdx.x * (blockDim.x * kFreeScan); h0 < num_buckets; h0 += gridDim.x * (blockDim.x * kFreeScan)) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    Bucket b[kFreeScan];
+    unsigned long long found[kFreeScan];
+    uint32_t n = 0;
+#pragma unroll
+    for (int q = 0; q < kFreeScan; ++q) {
+      const uint32_t h = h0 + q * blockDim.x + threadIdx.x;
+      b[q] = m.buckets[min(h, num_buckets - 1u)];
+    }
+#pragma unroll
+    for (int q = 0; q < kFreeScan; ++q) {
+      const uint32_t h = h0 + q * blockDim.x + threadIdx.x;
+      found[q] = __ballot(h < num_buckets && b[q].key != kEmptyKey && is_free_slot(b[q].slot));
+      n += (uint32_t)__popcll(found[q]);
+    }
+    uint32_t at = 0;
+    if (lane == 0 && n) at = atomicAdd(&s_n, n);  // LDS
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) s_base = atomicAdd(count, s_n);
+    __syncthreads();
+    at = s_base + (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+    for (int q = 0; q < kFreeScan; ++q) {
+      const uint32_t i = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(found[q] >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)found[q], 0u));
+      at += (uint32_t)__popcll(found[q]);
+      if (!((found[q] >> lane) & 1ull) || i >= cap) continue;
+      int x, y, z;
+      unpack_key(b[q].key, x, y, z);
+      keys[3 * (size_t)i] = x;
+      keys[3 * (size_t)i + 1] = y;
+      keys[3 * (size_t)i + 2] = z;
+      if (w) w[i] = (float)(b[q].slot & 0xFFu);
+    }
+    __syncthreads();  // s_n and s_base are used again
   }
 }
 
 void launch_export_free(const MapDev& m, uint32_t num_buckets, int32_t* keys, float* w, uint32_t cap, uint32_t* count,
                         hipStream_t s) {
   zero_u32_kernel<<<1, 64, 0, s>>>(count);
-  export_free_kernel<<<2048, 256, 0, s>>>(m, num_buckets, keys, w, cap, count);
+  const uint32_t per = 256 * kFreeScan, grid = (num_buckets + per - 1) / per;
+  export_free_kernel<<<grid < 2048 ? grid : 2048, 256, 0, s>>>(m, num_buckets, keys, w, cap, count);
 }
 
 void launch_frame_blocks(const MapDev& m, int32_t* keys, uint32_t cap, uint32_t* count, hipStream_t s) {
