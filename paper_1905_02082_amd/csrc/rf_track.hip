@@ -1004,7 +1004,13 @@ __global__ __launch_bounds__(kTrackBlock) void residual_kernel(Batch b, float ga
     xform(R, t, x, y);
     float S, Iv, g3[3], h3[3];
     int mark;  // nothing is written back
-    if (sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3, CachedSlots<SLOTS>{cache, &mark})) {
+    // a tile without pairs (a map that has not tracked at this level) has nothing
+    // to gain from filling a cache that is not kept: 640x480 18.0 us through it,
+    // 12.9 without; 1280x720 31 and 22.8; with its pairs 8.8
+    const bool defined = s_cache.cnt != 0 ? sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3,
+                                                                            CachedSlots<SLOTS>{cache, &mark})
+                                          : sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3);
+    if (defined) {
       r = S * S;
       out = (r > gamma * (m.tau * m.tau)) ? 1 : 0;
     }

@@ -92,3 +92,25 @@ def test_block_cache_over_jumping_frames(rf, voxel, tau, adaptive):
         b = run(fresh, k, start)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
         assert a[1][28] > 1000
+
+
+@pytest.mark.parametrize("free_blocks", [False, True])
+@pytest.mark.parametrize("width,height", [(320, 240), (77, 53)])
+def test_residual_with_and_without_cached_pairs(rf, width, height, free_blocks):
+    """The mask's residual on a map that has not tracked (tiles look up the
+    hash table) and on one that has (through the tile cache) is the same."""
+    seq = synth.static_room(n_frames=5, width=width, height=height)
+    mp = map_params(rf, seq, max_blocks=1 << 16)
+    mp.free_blocks = free_blocks
+    res = []
+    for tracked in (False, True):
+        m = rf.Map(mp)
+        build(rf, m, seq, range(3))
+        if tracked:
+            track(rf, m, seq, 4, 2)
+        out = torch.empty((height, width), dtype=torch.float32, device="cuda")
+        P = torch.as_tensor(seq.poses[4]).cuda().contiguous()
+        m.dynamic_mask(gpu_frame(rf, seq, 4), P, rf.MaskParams(), residual=out)
+        res.append(out.cpu().numpy())
+    assert (res[0] >= 0).sum() > res[0].size // 4
+    assert np.array_equal(res[0], res[1])
