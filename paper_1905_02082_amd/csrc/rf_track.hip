@@ -179,7 +179,7 @@ __device__ __forceinline__ int tri_index(int i, int j) {  // H(i,j), i <= j, pac
 // Every lane solves the whole system: a dependent chain, in which passing rows
 // between lanes costs more than the arithmetic it would save (a row a lane took
 // 96 lane reads and a branch a pivot; with the range test a ballot and the
-// exponential applied as cross products, 3250 -> 2000 cycles from totals to
+// exponential applied as cross products, 3250 -> 2100 cycles from totals to
 // pose).
 __device__ __forceinline__ void solve_update_wave(const double* s_ne, const TrackArgs& a, const double* Tin,
                                                   double* s_T, float* s_Tf, int* s_state) {
@@ -385,7 +385,7 @@ __device__ __forceinline__ void solve_step(const MapDev& m, double* user_pose, c
   }
 }
 
-// Per-workgroup block cache in LDS: a direct-mapped window of kWin^3 blocks
+// Per-workgroup block cache in LDS: a direct-mapped window of win^3 blocks
 // centred on the bounding box of the tile's cached blocks (one indexed read,
 // no key to compare) and, for blocks outside it, a small open-addressing
 // hash (linear probing).  Built from the tile's cached pairs before the first
@@ -396,13 +396,18 @@ __device__ __forceinline__ void solve_step(const MapDev& m, double* user_pose, c
 // yield a wrong slot.
 constexpr int kNoSlot = (int)0x80000000;
 constexpr int kMaxProbe = 8;   // a key is placed within 8 slots of its home or not cached
-constexpr int kWin = 8;        // direct-mapped window of kWin^3 blocks around the tile's blocks
-constexpr int kWinCells = kWin * kWin * kWin;
+// Direct-mapped window of win^3 blocks around the tile's blocks.  A tile of the
+// coarsest levels (64 pixels of a 640-pixel row and more) is up to 11 blocks wide at
+// 0.5 cm; with 8 most of its lookups went on to the LDS hash and the table:
+// with 16 a 640x480 step takes 965 us instead of 996 at 0.5 cm, 746 instead of
+// 775 at 1 cm.  The finer levels' tiles fit 8, which clears faster.
+__host__ __device__ constexpr int win_of(int slots) { return slots >= 512 ? 16 : 8; }
 constexpr int kFarOrigin = 0x40000000;  // window origin that no block coordinate reaches
 
 // SLOTS: LDS hash capacity (the tile's pair capacity at the launch's level).
 template <int SLOTS>
 struct TileCache {
+  static constexpr int kWin = win_of(SLOTS);
   unsigned long long* key;  // SLOTS, kEmptyKey when free
   int* slot;                // SLOTS, kNoSlot until written
   uint8_t* used;            // SLOTS, 1 when looked up in this launch
@@ -460,11 +465,12 @@ struct TileCache {
 // eight reads at the corners' own cells: no key, no comparison, no choice among
 // the distinct blocks' slots.  Their window cells are marked as used only when
 // the tile's cache is written back (mark: the lower corner's cell, with the
-// crossed block faces from bit 9; -1 without a lookup to mark), since most
+// crossed block faces from bit 12; -1 without a lookup to mark), since most
 // launches don't.  A lookup of separate tests per corner took 2700 of a
 // workgroup's 18000 cycles.
 template <int SLOTS>
 struct CachedSlots {
+  static constexpr int kWin = win_of(SLOTS);
   TileCache<SLOTS> c;
   int* mark;
   __device__ __forceinline__ bool operator()(const MapDev& m, int bx0, int by0, int bz0, int cross, int sl[8]) const {
@@ -480,7 +486,7 @@ struct CachedSlots {
 #pragma unroll
     for (int k = 1; k < 8; ++k) least = min(least, sl[k]);
     if (in && least != kNoSlot) {  // kNoSlot is the lowest value
-      *mark = (int)(g - c.grid) | cross << 9;
+      *mark = (int)(g - c.grid) | cross << 12;
     } else {
       general(m, bx0, by0, bz0, cross, sl);
     }
@@ -539,12 +545,14 @@ struct CachedSlots {
 };
 
 // Marks the window cells of a lookup (CachedSlots::mark) as used.
+template <int WIN>
 __device__ __forceinline__ void mark_used(uint8_t* gused, int mark) {
   if (mark < 0) return;
-  const int cl = mark & (kWinCells - 1), cross = mark >> 9;
+  const int cl = mark & 4095, cross = mark >> 12;
+  static_assert(WIN * WIN * WIN <= 4096, "cell and faces fit 15 bits");
 #pragma unroll
   for (int k = 0; k < 8; ++k)
-    gused[cl + (k & cross & 1) + kWin * ((k & cross) >> 1 & 1) + kWin * kWin * ((k & cross) >> 2)] = 1;
+    gused[cl + (k & cross & 1) + WIN * ((k & cross) >> 1 & 1) + WIN * WIN * ((k & cross) >> 2)] = 1;
 }
 
 // LDS of a tile's cache and the wavefront that fills it: the tile's cached
@@ -553,6 +561,7 @@ __device__ __forceinline__ void mark_used(uint8_t* gused, int mark) {
 // holds the window's origin, set when the pairs were written.
 template <int SLOTS>
 struct CacheLds {
+  static constexpr int kWin = win_of(SLOTS), kWinCells = kWin * kWin * kWin;
   alignas(16) unsigned long long hk[SLOTS];
   alignas(16) int hs[SLOTS];
   alignas(16) uint8_t used[SLOTS];
@@ -562,7 +571,7 @@ struct CacheLds {
   int miss;
   int cnt;               // pairs loaded
   uint32_t nref;         // pairs written back
-  uint32_t cells;        // their bounding box: the window's x, y and z in use (8 bits each),
+  uint32_t cells[2];     // their bounding box: the window's x and y, and z, in use (16 bits each),
   int lo[3], hi[3];      // and the blocks outside the window
 
   __device__ __forceinline__ TileCache<SLOTS> cache(int ax, int ay, int az) {
@@ -575,6 +584,7 @@ __device__ __forceinline__ void build_tile_cache(const BlockRef* tab, const uint
                                                  uint32_t epoch, int lane, CacheLds<SLOTS>& L) {
   const BlockRef none{kEmptyKey, -1, 0u};
   constexpr int kLoads = SLOTS / 64;
+  constexpr int kWinCells = CacheLds<SLOTS>::kWinCells;
   const int cnt = cached ? (int)min(*tcount, (uint32_t)(nrefs - 1)) : 0;
   BlockRef e[kLoads];
 #pragma unroll
@@ -604,7 +614,7 @@ __device__ __forceinline__ void build_tile_cache(const BlockRef* tab, const uint
   if (lane == 0) {
     L.miss = 0;
     L.cnt = cnt;
-    L.nref = L.cells = 0u;
+    L.nref = L.cells[0] = L.cells[1] = 0u;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       L.org[d] = org[d];
@@ -636,6 +646,7 @@ __device__ __forceinline__ void build_tile_cache(const BlockRef* tab, const uint
 template <int SLOTS>
 __device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount, int nrefs, uint32_t epoch,
                                                  CacheLds<SLOTS>& L) {
+  constexpr int kWin = CacheLds<SLOTS>::kWin, kWinCells = CacheLds<SLOTS>::kWinCells;
   const int lane = threadIdx.x & 63;
   // one position counter atomic per wavefront
   auto keep = [&](bool yes, unsigned long long key, int slot) {
@@ -657,18 +668,27 @@ __device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount
   // 933 / 1202.
   const bool all = 2 * L.cnt < nrefs, few = 4 * L.cnt < nrefs;
   // the window's cells in use, a bit per x, y and z
-  uint32_t cells = 0;
+  uint32_t cells[2] = {0u, 0u};
 #pragma unroll
   for (int q = 0; q < kWinCells / kTrackBlock; ++q) {
     const int h = threadIdx.x + q * kTrackBlock;
     const int ss = L.grid[h], x = h % kWin, y = (h / kWin) % kWin, z = h / (kWin * kWin);
     const bool yes = ss != kNoSlot && L.gused[h];
     keep(yes || (all && ss != kNoSlot), pack_key(L.org[0] + x, L.org[1] + y, L.org[2] + z), ss);
-    if (yes) cells |= 1u << x | 256u << y | 65536u << z;
+    if (yes) {
+      cells[0] |= 1u << x | 65536u << y;
+      cells[1] |= 1u << z;
+    }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cells |= (uint32_t)__shfl_xor((int)cells, o);
-  if (lane == 0 && cells) atomicOr(&L.cells, cells);
+  for (int o = 32; o > 0; o >>= 1) {
+    cells[0] |= (uint32_t)__shfl_xor((int)cells[0], o);
+    cells[1] |= (uint32_t)__shfl_xor((int)cells[1], o);
+  }
+  if (lane == 0 && cells[1]) {
+    atomicOr(&L.cells[0], cells[0]);
+    atomicOr(&L.cells[1], cells[1]);
+  }
   for (int h0 = 0; h0 < SLOTS; h0 += kTrackBlock) {
     const int h = h0 + threadIdx.x;
     const unsigned long long kk = L.hk[h];
@@ -706,7 +726,7 @@ __device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount
     int org[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      const uint32_t c = (L.cells >> (8 * d)) & 255u;
+      const uint32_t c = (L.cells[d >> 1] >> (d == 1 ? 16 : 0)) & 0xFFFFu;
       const int lo = min(L.lo[d], c ? L.org[d] + __ffs((int)c) - 1 : INT_MAX);
       const int hi = max(L.hi[d], c ? L.org[d] + 31 - __clz((int)c) : INT_MIN);
       org[d] = n ? ((lo + hi) >> 1) - (kWin / 2 - 1) : 0;
@@ -959,7 +979,7 @@ __global__ __launch_bounds__(kTrackBlock, SOLVE ? 5 : 6) void track_kernel(Batch
     }
   }
   if (cached && s_cache.miss) {  // uniform
-    mark_used(s_cache.gused, (int16_t)s_mark[threadIdx.x]);
+    mark_used<win_of(SLOTS)>(s_cache.gused, (int16_t)s_mark[threadIdx.x]);
     __syncthreads();
     write_tile_cache<SLOTS>(tab, tcount, nrefs, epoch, s_cache);
   }
