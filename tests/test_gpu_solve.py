@@ -64,3 +64,22 @@ def test_solve_at_every_place(rf, scene):
         m.track(g, Q, rf.TrackParams(1, 1))
     torch.cuda.synchronize()
     assert np.array_equal(P.cpu().numpy(), Q.cpu().numpy())
+
+
+@pytest.mark.parametrize("adaptive", [False, True])
+@pytest.mark.parametrize("lam", [1e200, 1e300, 1e308, np.inf])
+def test_damping_without_bound_keeps_the_pose(rf, scene, lam, adaptive):
+    """Damping up to infinity is accepted: the reciprocal pivots go to zero, so
+    every step is applied and changes nothing.  Steps are at most |g| / (lambda
+    min diag H) < 1e20 / 1e200 per component; an infinite damping gives exactly
+    zero.  Under Levenberg-Marquardt the first step starts from lambda itself."""
+    seq, m = scene
+    P = dev_pose(seq.poses[0])
+    stats = torch.zeros(16, dtype=torch.float64, device="cuda")
+    n = 2 if adaptive else 3
+    m.track(gpu_frame(rf, seq, 1), P, rf.TrackParams(1, n, lm_lambda=lam, adaptive=adaptive), None, stats)
+    words = stats.cpu().numpy().view(np.uint32)
+    assert int(words[5]) == 0                                          # no flag
+    assert int(words[4]) == (1 if adaptive else 3)                     # steps counted
+    d = np.abs(P.cpu().numpy() - seq.poses[0]).max()
+    assert d == 0.0 if np.isinf(lam) else d <= 1e-150
