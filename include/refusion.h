@@ -214,7 +214,9 @@ rf_status compute_dynamic_mask_static(rf_map* m, const rf_frame* f, const double
                                       uint8_t* d_mask_out, float* d_residual_out, void* stream);
 
 /* compute_dynamic_mask that also writes its intermediate masks (each nullable,
- * device uint8 width*height): raw threshold, eroded seeds M_R, flood fill M_D. */
+ * device uint8 width*height): raw threshold, eroded seeds M_R, flood fill M_D.
+ * Outputs given the same buffer leave the last of them (in this order, then
+ * the mask) in it. */
 rf_status compute_dynamic_mask_stages(rf_map* m, const rf_frame* f, const double* d_pose,
                                       const rf_mask_params* mp, uint8_t* d_raw, uint8_t* d_eroded,
                                       uint8_t* d_filled, uint8_t* d_mask_out, float* d_residual_out,

@@ -366,8 +366,13 @@ rf_status compute_dynamic_mask_stages(rf_map* m, const rf_frame* f, const double
   auto fill = [&](const rf_job& jj, rf::Job& J) -> rf_status {
     rf_status s2 = mask_checks(jj, J);
     if (s2) return s2;
-    J.raw = d_raw;
-    J.eroded = d_eroded;
+    // Callers may give stages the same buffer, which then keeps the last one
+    // written to it (raw, eroded, filled, mask).  The fill's first kernel reads
+    // the raw plane around a tile while others write their erosion, so the two
+    // never share a plane: an erosion that the mask replaces is not written,
+    // and a raw decision that the erosion replaces goes to the mask's plane.
+    J.raw = d_raw == d_eroded ? nullptr : d_raw;
+    J.eroded = d_eroded == d_mask_out ? nullptr : d_eroded;
     J.filled = d_filled;
     J.residual = d_residual_out;
     return RF_OK;
