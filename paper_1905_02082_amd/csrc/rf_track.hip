@@ -669,6 +669,7 @@ __device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount
   // 954 / 1216 us, all below half 929 / 1280, window only 948 / 1205, this rule
   // 933 / 1202.
   const bool all = 2 * L.cnt < nrefs, few = 4 * L.cnt < nrefs;
+  static_assert(kWinCells % kTrackBlock == 0, "the walk over the window ends with it");
   // the window's cells in use, a bit per x, y and z
   uint32_t cells[2] = {0u, 0u};
 #pragma unroll
@@ -692,10 +693,13 @@ __device__ __forceinline__ void write_tile_cache(BlockRef* tab, uint32_t* tcount
     atomicOr(&L.cells[1], cells[1]);
   }
   for (int h0 = 0; h0 < SLOTS; h0 += kTrackBlock) {
-    const int h = h0 + threadIdx.x;
+    // every lane takes part in keep(); with more threads than slots those
+    // beyond the hash have nothing
+    const bool in = SLOTS % kTrackBlock == 0 || h0 + (int)threadIdx.x < SLOTS;
+    const int h = in ? h0 + threadIdx.x : 0;
     const unsigned long long kk = L.hk[h];
     const int ss = L.hs[h];
-    const bool known = kk != kEmptyKey && ss != kNoSlot, yes = known && L.used[h];
+    const bool known = in && kk != kEmptyKey && ss != kNoSlot, yes = known && L.used[h];
     keep(yes || (few && known), kk, ss);
     const unsigned long long bal = __ballot(yes);
     if (bal == 0ull) continue;  // uniform
