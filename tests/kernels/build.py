@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 LIB = os.path.join(HERE, "libtest_kernels.so")
 # source -> options of its own
-SOURCES = {"tile_cache.hip": ["-DRF_TRACK_BLOCK=512"]}
+SOURCES = {"tile_cache.hip": ["-DRF_TRACK_BLOCK=512"], "reciprocals.hip": []}
 
 
 def build() -> str:

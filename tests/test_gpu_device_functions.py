@@ -64,3 +64,33 @@ def test_tile_cache_of_512_threads_keeps_its_pairs(kernels, slots, nrefs, n):
         slot = (t[1:n + 1, 1] & 0xFFFFFFFF).astype(np.int64)
         assert sorted(map(tuple, np.c_[got, slot])) == sorted(map(tuple, np.c_[blocks, np.arange(n)]))
         assert (t[n + 1:] == 0).all()            # nothing past them
+
+
+def test_reciprocal_of_every_float(kernels):
+    """rcp_rn, on which the integration's bit-exactness rests: the IEEE 1 / x for
+    all 2^32 bit patterns (any NaN for a NaN)."""
+    bad = torch.zeros(1, dtype=torch.int64, device="cuda")
+    assert kernels.check_rcp_f32(ctypes.c_void_p(bad.data_ptr()), stream()) == 0
+    assert int(bad.item()) == 0
+
+
+@pytest.mark.parametrize("e0,ne", [(-100, 200), (-1000, 2000)])
+def test_reciprocal_of_doubles(kernels, e0, ne):
+    """rcp_f64, the solve's reciprocal pivots: the division for 2^32 random
+    values, over the magnitudes of pivots and over nearly all normal ones."""
+    bad = torch.zeros(1, dtype=torch.int64, device="cuda")
+    assert kernels.check_rcp_f64(e0, ne, ctypes.c_void_p(bad.data_ptr()), stream()) == 0
+    assert int(bad.item()) == 0
+
+
+def test_reciprocal_of_special_doubles(kernels):
+    x = np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 1.0, -3.0, 2.0 ** -1000, 2.0 ** 1000])
+    with np.errstate(divide="ignore"):
+        want = 1.0 / x
+    dx = torch.from_numpy(x).cuda()
+    dy = torch.zeros_like(dx)
+    rc = kernels.rcp_f64_values(ctypes.c_void_p(dx.data_ptr()), ctypes.c_void_p(dy.data_ptr()), len(x), stream())
+    assert rc == 0
+    y = dy.cpu().numpy()
+    np.testing.assert_array_equal(y, want)
+    assert (np.signbit(y) == np.signbit(want))[~np.isnan(x)].all()
