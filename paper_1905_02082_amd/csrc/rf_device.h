@@ -425,6 +425,13 @@ __device__ __forceinline__ float quotient_rn(float a, float b, float y) {
   return __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q);
 }
 
+// The same for any a and b: products that overflow (the correction would form
+// inf - inf), infinite and zero divisors give what the division gives.  One
+// instruction more, so the projections, whose test rejects those, do without.
+__device__ __forceinline__ float quotient_any(float a, float b, float y) {
+  return __builtin_amdgcn_div_fixupf(quotient_rn(a, b, y), b, a);
+}
+
 // Float copy of the FP64 pose: R row-major, t.
 __device__ __forceinline__ void load_pose_f(const double* T, float R[9], float t[3]) {
 #pragma unroll

@@ -840,7 +840,7 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
             }
           }
         }
-        nsdf[v] = quotient_rn(W[v] * sdf[v] + dval, W[v] + 1.0f, rw[v]);
+        nsdf[v] = quotient_any(W[v] * sdf[v] + dval, W[v] + 1.0f, rw[v]);
       }
       // pending free blocks: a band update anywhere in the block gives it a pool
       // slot (all its voxels are then written); otherwise the frame counts for
@@ -946,8 +946,8 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
           uint32_t c = 0u;
 #pragma unroll
           for (int q = 0; q < 3; ++q)
-            c |= (uint32_t)fminf(255.0f, fmaxf(0.0f, rintf(quotient_rn(Wv * (float)((col[j] >> (8 * q)) & 0xFFu) +
-                                                                           (float)cpx[v][q], Wn, rw[v]))))
+            c |= (uint32_t)fminf(255.0f, fmaxf(0.0f, rintf(quotient_any(Wv * (float)((col[j] >> (8 * q)) & 0xFFu) +
+                                                                            (float)cpx[v][q], Wn, rw[v]))))
                  << (8 * q);
           col[j] = c;
         }

@@ -189,6 +189,39 @@ def test_integration_of_imported_weights(rf, W, H, dx):
     np.testing.assert_array_equal(gc[~huge], c32[~huge])
 
 
+@pytest.mark.parametrize("big", [1.0e36, 3.0e38, np.inf])
+def test_integration_of_weights_whose_products_overflow(rf, big):
+    """Imported weights so large that W c, or W sdf, overflows: sdf, weight and
+    colour of every voxel are what the FP32 mirror's division makes of them."""
+    rng = np.random.default_rng(3)
+    s, tau, W, H = 0.02, 0.06, 64, 48
+    keys = np.array([[x, y, z] for x in range(-3, 3) for y in range(-3, 3) for z in range(-1, 8)], np.int32)
+    shape = (len(keys), 512)
+    sdf = rng.uniform(-tau, tau, shape).astype(np.float32)
+    sdf[rng.uniform(size=shape) < 0.1] = 1.0e5
+    w = rng.choice(np.array([1.0, big], np.float32), shape)
+    rgb = rng.integers(0, 256, shape + (3,)).astype(np.uint8)
+    rgb[rng.uniform(size=shape + (3,)) < 0.1] = 0
+    intr = (50.0, 50.0, (W - 1) / 2.0, (H - 1) / 2.0)
+    depth = (0.7 + 0.2 * rng.uniform(size=(H, W))).astype(np.float32)
+    img = rng.integers(0, 256, (H, W, 3)).astype(np.uint8)
+    T = np.eye(4)
+    m = rf.Map(rf.MapParams(s, tau, 5.0, 1 << 12, 1 << 11, 255, 2, "fp32", W * H))
+    m.import_(*[torch.from_numpy(x).cuda() for x in (keys, sdf, w, rgb)])
+    o = O.OracleMap(s, tau, 5.0, 255, 2, real_bits=32)
+    o.import_(keys, sdf.astype(np.float64), w.astype(np.float64), rgb)
+    m.allocate(gf := rf.Frame.from_numpy(depth, img, *intr), dev_pose(T))
+    m.integrate(gf, dev_pose(T))
+    o.allocate(O.Frame(depth, img, *intr), T)
+    o.integrate(O.Frame(depth, img, *intr), T)
+    gk, gs, gw, gc = gpu_export_sorted(m)
+    k, s32, w32, c32 = o.export()
+    assert np.array_equal(gk, k) and (gw == 255.0).any()
+    np.testing.assert_array_equal(gw, w32.astype(np.float32))
+    np.testing.assert_array_equal(gs, s32.astype(np.float32))
+    np.testing.assert_array_equal(gc, c32)
+
+
 def test_integration_masked_pixels_untouched(rf, room):
     rng = np.random.default_rng(1)
     mask = np.zeros((room.height, room.width), np.uint8)
