@@ -176,6 +176,8 @@ rf_status mask_checks(const rf_job& j, rf::Job& J) {
   const uint32_t tiles =
       (uint32_t)((J.f.W + rf::kTile - 1) / rf::kTile) * (uint32_t)((J.f.H + rf::kTile - 1) / rf::kTile);
   if (tiles > j.map->h.dev.dirty_cap) return fail(RF_ENOMEM, "flood-fill tile table too small");
+  if (align256(rf::flood_edge_bytes(J.f)) > rf::flood_edge_room(j.map->h.dev.tc_tiles))
+    return fail(RF_ENOMEM, "flood-fill scratch too small");
   J.pose = j.d_pose;
   J.mask_out = j.d_mask_out;
   return RF_OK;

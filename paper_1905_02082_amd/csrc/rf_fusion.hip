@@ -775,8 +775,8 @@ __global__ __launch_bounds__(256) void integrate_kernel(Batch b) {
         const float vf = f.fy * quotient_rn(x1, x2, iz) + f.cy;
         const float ur = floorf(uf + 0.5f), vr = floorf(vf + 0.5f);
         in = in && ur >= 0.0f && ur < (float)f.W && vr >= 0.0f && vr < (float)f.H;
-        // vr < H and W are below 2^24 whenever the product is below 2^26 (the
-        // frame's limit), so the 24-bit multiply is exact
+        // vr < H and W are at most 2^22 (a frame has at most 2^18 tiles of 16x16
+        // pixels, make_frame), so the 24-bit multiply is exact
         pix[v] = in ? (int)(__umul24((uint32_t)(int)vr, (uint32_t)f.W) + (uint32_t)(int)ur) : 0;
         X2[v] = x2;
         vis[v] = in;

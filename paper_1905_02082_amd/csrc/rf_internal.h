@@ -70,6 +70,7 @@ void launch_normal_equations(Batch& b, int depth_format, int storage, int level,
 void launch_mask(Batch& b, int depth_format, int storage, const rf_mask_params& mp, void* edges, hipStream_t s);
 size_t flood_edge_bytes(const FrameDev& f);    // 8 bits a pixel, lines padded to words
 size_t flood_member_bytes(const FrameDev& f);  // 1 bit a pixel
+size_t flood_edge_room(uint32_t tc_tiles);     // what the map's own scratch holds of the rule's bits
 // residual and raw decision of the mask (its first stage), through the tracking tile cache
 void launch_residual(Batch& b, int depth_format, int storage, float gamma, hipStream_t s);
 

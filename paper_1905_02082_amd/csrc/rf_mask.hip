@@ -401,6 +401,15 @@ size_t flood_edge_bytes(const FrameDev& f) {
   return (size_t)F.nx * F.nv * 64;
 }
 
+// Bytes of the last level's pairs: 8192 a tile.  Every frame of up to
+// max_pixels pixels fits: its bits take 64 bytes for each 64 pixels of a line or
+// part of them, so a line of at least 64 pixels takes less than 2 bytes a
+// pixel, where a map has 8192 for each 256 pixels, and the frames whose longer
+// side is shorter take less than 4096, which the map's 64 spare tiles hold.
+size_t flood_edge_room(uint32_t tc_tiles) {
+  return (size_t)tile_refs(kCacheLevels - 1) * tc_tiles * sizeof(BlockRef);
+}
+
 size_t flood_member_bytes(const FrameDev& f) {
   FloodJob F;
   flood_axes(f, F);
@@ -427,9 +436,9 @@ void launch_mask(Batch& b, int df, int st, const rf_mask_params& mp, void* edges
       // The end of the tracking cache: its last level has pairs for as many
       // tiles as the finest, of which a frame uses one in 64, so the pairs of
       // the last tiles are free (thin frames may reach them: their counts are
-      // cleared).  A frame's bits always fit (at most 4 bytes a pixel of 32).
+      // cleared).  The caller has checked that the bits fit (flood_edge_room).
       const size_t bytes = (flood_edge_bytes(J.f) + 255) & ~(size_t)255;
-      const size_t region = (size_t)tile_refs(kCacheLevels - 1) * J.m.tc_tiles * sizeof(BlockRef);
+      const size_t region = flood_edge_room(J.m.tc_tiles);
       char* end = reinterpret_cast<char*>(J.m.tcache + (size_t)tile_refs_before(kCacheLevels) * J.m.tc_tiles);
       F.edge = reinterpret_cast<u64*>(end - bytes);
       F.clear_from = (int)((region - bytes) / (tile_refs(kCacheLevels - 1) * sizeof(BlockRef)));
