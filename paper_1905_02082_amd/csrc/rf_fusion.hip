@@ -286,9 +286,11 @@ union AllocLds {
   unsigned long long band[4][kBandWalk][64];  // per wavefront
 };
 
-// The band segments of a 16x16 pixel tile, a wavefront on each 8x8 pixels.
-template <int DF>
-__device__ __forceinline__ void alloc_band(const Job& J, int g, AllocLds& L, unsigned long long* queue) {
+// The segments of a 16x16 pixel tile, a wavefront on each 8x8 pixels, which
+// walks and takes its own rays' cells in turn: the band segments of the pixels
+// off the carve grid, or (CARVE) every pixel's carve segment.
+template <int DF, bool CARVE>
+__device__ __forceinline__ void alloc_rays(const Job& J, int g, AllocLds& L, unsigned long long* queue) {
   const FrameDev& f = J.f;
   const MapDev& m = J.m;
   const int s_c = (int)m.carve_stride;
@@ -298,7 +300,8 @@ __device__ __forceinline__ void alloc_band(const Job& J, int g, AllocLds& L, uns
   Dda d;
   d.left = 0;
   unsigned long long key = 0, skey[3] = {0, 0, 0};
-  if (u < f.W && v < f.H && !(u % s_c == 0 && v % s_c == 0) && start_ray<DF>(J, u, v, false, d)) ray_keys(d, key, skey);
+  const bool mine = u < f.W && v < f.H && (CARVE || !(u % s_c == 0 && v % s_c == 0));
+  if (mine && start_ray<DF>(J, u, v, CARVE, d)) ray_keys(d, key, skey);
   else d.left = 0;
   uint8_t* touched = touched_map(m);
   CellQueue q{queue, 0};
@@ -369,7 +372,9 @@ __device__ __forceinline__ void alloc_carve(const Job& J, int g, AllocLds& L, in
   q.finish(m, touched);
 }
 
-template <int DF>
+// OWN: some job's carve rays are walked by wavefronts of their own
+// (kSharedCarve); without it that path is compiled out.
+template <int DF, bool OWN>
 __global__ __launch_bounds__(256, 6) void alloc_kernel(Batch b) {
   // Per job: workgroups [0, carve_groups) take the carve segments of the
   // carve-grid pixels, the rest the band segments of the other pixels; the
@@ -388,8 +393,9 @@ __global__ __launch_bounds__(256, 6) void alloc_kernel(Batch b) {
     advance_epoch(J.m.st);
   }
   unsigned long long* queue = s_queue[threadIdx.x >> 6];
-  if (g < J.carve_groups) alloc_carve<DF>(J, g, s_rays, s_more, queue);
-  else alloc_band<DF>(J, g - J.carve_groups, s_rays, queue);
+  if (g >= J.carve_groups) alloc_rays<DF, false>(J, g - J.carve_groups, s_rays, queue);
+  else if (OWN && J.carve_own) alloc_rays<DF, true>(J, g, s_rays, queue);
+  else alloc_carve<DF>(J, g, s_rays, s_more, queue);
 }
 
 // The frame's block list: every bucket marked as touched, appended in runs
@@ -1012,20 +1018,46 @@ __global__ __launch_bounds__(256) void integ_fold_kernel(Batch b) {
 }
 
 // ------------------------------------------------------------ host launchers
+// With a carve ray per pixel there are no band rays to fill the CUs while one
+// wavefront in four walks, so launches of more workgroups of 64 shared carve
+// rays than this (all jobs together; some two rounds of what is resident) give
+// each wavefront rays of its own.  On a loaded map, shared / own: 320x240 at 1 cm
+// (1200) 24 / 43 us, 640x480 (4800) at 2, 1 and 0.5 cm 36.4 / 29.7, 48.6 / 46.2
+// and 75.8 / 79.9, 1280x720 (14400) 106 / 79; on an empty map own is faster from
+// 640x480 on (84 / 57).  With band rays beside them shared walks stay ahead (two
+// by two, four sessions of 640x480 at 0.5 cm, 4800: 96 / 109).
+constexpr int kSharedCarve = 4096;
+
 void launch_allocate(Batch& b, int depth_format, hipStream_t s) {
-  int total = 0;
+  int shared = 0;
   for (int j = 0; j < b.n; ++j) {
     Job& J = b.job[j];
     const int sc = (int)J.m.carve_stride;
     J.carve_w = (J.f.W + sc - 1) / sc;
     J.carve_h = (J.f.H + sc - 1) / sc;
     J.carve_groups = ((J.carve_w + kRayTile - 1) / kRayTile) * ((J.carve_h + kRayTile - 1) / kRayTile);
+    shared += J.carve_groups;
+  }
+  int total = 0;
+  bool own = false;
+  for (int j = 0; j < b.n; ++j) {
+    Job& J = b.job[j];
+    const int tiles = ((J.f.W + 15) / 16) * ((J.f.H + 15) / 16);
+    const bool every = J.m.carve_stride == 1;  // no band rays
+    J.carve_own = every && shared > kSharedCarve;
+    if (J.carve_own) J.carve_groups = tiles;
+    own = own || J.carve_own;
     b.base[j] = total;
-    total += J.carve_groups + ((J.f.W + 15) / 16) * ((J.f.H + 15) / 16);
+    total += J.carve_groups + (every ? 0 : tiles);
   }
   b.base[b.n] = total;
-  if (depth_format == RF_DEPTH_U16) alloc_kernel<RF_DEPTH_U16><<<total, 256, 0, s>>>(b);
-  else alloc_kernel<RF_DEPTH_F32><<<total, 256, 0, s>>>(b);
+  auto run = [&](auto with_own) {
+    constexpr bool O = decltype(with_own)::value;
+    if (depth_format == RF_DEPTH_U16) alloc_kernel<RF_DEPTH_U16, O><<<total, 256, 0, s>>>(b);
+    else alloc_kernel<RF_DEPTH_F32, O><<<total, 256, 0, s>>>(b);
+  };
+  if (own) run(std::true_type{});
+  else run(std::false_type{});
   const int per = kListGroups / b.n;
   for (int j = 0; j <= b.n; ++j) b.base[j] = j * per;
   list_frame_kernel<<<b.n * per, 256, 0, s>>>(b);

@@ -32,6 +32,7 @@ struct Job {
   float* residual;
   int carve_groups;         // allocation: workgroups of carve rays (before the band rays')
   int carve_w, carve_h;     // allocation: carve-grid size
+  int carve_own;            // allocation: carve rays walked by wavefronts of their own (a ray per pixel)
   int cells_w, cells_h;     // integration of a compact free-space map: 8x8 depth cells of the frame
 };
 

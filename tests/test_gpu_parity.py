@@ -127,6 +127,40 @@ def test_allocated_blocks_over_ray_shapes(rf, W, H, stride, voxel, tau, dmax, fr
     assert m.status()[0] == 0 and m.num_keys() == o.num_blocks
 
 
+@pytest.mark.parametrize("sizes", [[(515, 513, 1)], [(361, 385, 1), (77, 53, 2), (361, 387, 1)]])
+def test_allocated_blocks_of_many_carve_rays(rf, sizes):
+    """More than 4096 workgroups of carve rays, a ray per pixel (one map, and
+    maps that pass the line together, with one of another stride between them):
+    wavefronts with rays of their own list the FP32 mirror's blocks, the line's
+    other side (each map alone) the same."""
+    rng = np.random.default_rng(len(sizes))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    maps, orcs, sess, frames, ofr, T = [], [], [], [], [], np.eye(4)
+    T[:3, 3] = [0.3, -0.1, 0.2]
+    for W, H, stride in sizes:
+        f = 0.8 * W
+        intr = (f, f, (W - 1) / 2.0, (H - 1) / 2.0)
+        uu, vv = np.meshgrid(np.arange(W), np.arange(H))
+        depth = 1.4 + 0.4 * np.sin(uu / 40.0) * np.cos(vv / 30.0)
+        depth = np.where(rng.uniform(size=(H, W)) < 0.05, 0.0, depth).astype(np.float32)
+        rgb = rng.integers(0, 255, (H, W, 3)).astype(np.uint8)
+        p = rf.MapParams(0.02, 0.06, 5.0, 1 << 16, 1 << 14, 255, stride, "fp16", W * H)
+        sess.append(rf.Session(p, T))
+        maps.append(rf.Map(p))
+        orcs.append(O.OracleMap(0.02, 0.06, 5.0, 255, stride, real_bits=32, storage=1))
+        frames.append(rf.Frame.from_numpy(depth, rgb, *intr))
+        ofr.append(O.Frame(depth, rgb, *intr, depth_scale=1.0))
+    for _ in range(2):                                                 # into an empty and a loaded map
+        jobs = rf._jobs(sess, frames)
+        assert rf.lib().hashmap_allocate_batch(jobs, len(sess), stream) == 0
+        for s, m, o, g, fr in zip(sess, maps, orcs, frames, ofr):
+            m.allocate(g, dev_pose(T))
+            ref = o.allocate(fr, T)
+            assert np.array_equal(gpu_keyset(s.map.frame_blocks()), ref)
+            assert np.array_equal(gpu_keyset(m.frame_blocks()), ref)
+            assert s.map.status() == (0, o.num_blocks)
+
+
 # ---------------------------------------------------------------- integration
 
 def test_integration_matches_oracle(rf, room):
