@@ -169,3 +169,18 @@ def test_registration_on_both_sides_of_a_resident_round(rf, n):
         for x, y in zip(a, b):
             assert np.array_equal(x, y)
     assert all(a[6][0] == 0 for a in alone)
+
+
+@pytest.mark.parametrize("n", [2, 3])
+def test_registration_on_both_sides_of_the_separate_solve(rf, n):
+    """Sessions of 640x480: two have 2400 workgroups at level 0 and solve at the
+    start of each, three have 3600, more than the 3072 from which on the solve
+    is a launch of its own; both give each session what it gets alone."""
+    seqs = [synth.dynamic_room(n_frames=3, width=640, height=480, n_clusters=1, seed=31 + i, movers="in_view")
+            for i in range(n)]
+    alone = run(rf, seqs, batched=False, start_offsets=(0,) * n)
+    mixed = run(rf, seqs, batched=True, start_offsets=(0,) * n)
+    for a, b in zip(alone, mixed):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+    assert all(a[6][0] == 0 for a in alone)

@@ -67,6 +67,34 @@ def test_solve_at_every_place(rf, scene):
 
 
 @pytest.mark.parametrize("adaptive", [False, True])
+def test_solve_in_a_launch_of_its_own(rf, adaptive):
+    """A level of 3600 workgroups (1280x720), above the 3072 from which on the
+    solve is a launch of its own: three Gauss-Newton steps at once equal three
+    passes of one step, whose only solve is the last launch's, and a pass of
+    four Levenberg-Marquardt evaluations equals itself after another pass has
+    left other contents in the state buffers."""
+    seq = synth.static_room(n_frames=2, width=1280, height=720)
+    m = rf.Map(map_params(rf, seq))
+    m.allocate(gpu_frame(rf, seq, 0), dev_pose(seq.poses[0]))
+    m.integrate(gpu_frame(rf, seq, 0), dev_pose(seq.poses[0]))
+    assert m.status()[0] == 0
+    g = gpu_frame(rf, seq, 1)
+    P, Q = dev_pose(seq.poses[0]), dev_pose(seq.poses[0])
+    if adaptive:
+        tp = rf.TrackParams(1, 4, lm_lambda=1e-3, adaptive=True)
+        m.track(g, P, tp)
+        m.track(g, dev_pose(seq.poses[0]), rf.TrackParams(2, 3, lm_lambda=10.0, adaptive=True))
+        m.track(g, Q, tp)
+    else:
+        m.track(g, P, rf.TrackParams(1, 3))
+        for _ in range(3):
+            m.track(g, Q, rf.TrackParams(1, 1))
+    torch.cuda.synchronize()
+    assert m.status()[0] == 0 and np.array_equal(P.cpu().numpy(), Q.cpu().numpy())
+    assert np.abs(P.cpu().numpy() - seq.poses[0]).max() > 1e-4         # it moved
+
+
+@pytest.mark.parametrize("adaptive", [False, True])
 @pytest.mark.parametrize("lam", [1e200, 1e300, 1e308, np.inf])
 def test_damping_without_bound_keeps_the_pose(rf, scene, lam, adaptive):
     """Damping up to infinity is accepted: the reciprocal pivots go to zero, so
