@@ -8,7 +8,7 @@
 //   flist        num_buckets x 4 B   bucket indices of the blocks the last allocation touched
 //   sdfw         max_blocks x 512 x  {f32 sdf, f32 weight} (FP32) | {f16 sdf/tau, u8 weight, pad} (FP16)
 //   rgb          max_blocks x 512 x  uchar4 (RGB + pad)
-//   partials     tracking: 3 buffers of 29 fixed-point accumulators (128 B apart) + 2 poses
+//   partials     tracking: 3 buffers of 29 fixed-point accumulators (128 B apart) + 2 poses + 2 Levenberg-Marquardt states
 //   mask scratch max_pixels bytes (the flood fill's members, a bit each) + two buffers of per-tile dirty flags
 //   tile refs    tracking block cache: per level l < kCacheLevels, tc_tiles x tile_refs(l) x 16 B {key, slot, epoch},
 //                then kCacheLevels x tc_tiles x 4 B pair counts (the end of the last level, which a frame's few

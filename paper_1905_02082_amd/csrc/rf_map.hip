@@ -17,8 +17,9 @@ __host__ __device__ __forceinline__ uint32_t map_mark(const MapDev& m, int stora
 // time; the others are still zero.  An arena whose state does not carry the
 // mark (a new map) is cleared whole.  One launch, all stores 16 bytes wide:
 // bound by what it writes.  Clearing the pool and the pairs whole, with a
-// launch per array, took 183 us of the 1329 that building a temporary 640x480
-// model of ten frames and casting its rays takes; with this 1113.
+// launch per array, took 179 us in eight kernels for the temporary model of ten
+// 640x480 frames, now 33 in two (of the whole call, with the gaps between the
+// launches, 1329 us became 1113).
 __global__ __launch_bounds__(256) void clear_map_kernel(MapDev m, uint32_t num_buckets, int storage, int whole) {
   const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, n = (size_t)gridDim.x * blockDim.x;
   const uint4 z = make_uint4(0, 0, 0, 0);
@@ -186,7 +187,7 @@ void launch_surface(const MapDev& m, int storage, float* pts, uint32_t cap, uint
 // read as, in no particular order (the buckets are scanned).  A workgroup takes
 // kFreeScan buckets a thread at a time, all asked for together, and one atomic
 // for the room of what it found: an atomic a wavefront and 64 buckets, all on
-// one counter, took 54 us for 2^20 buckets, this 9.
+// one counter, took 54.8 us for 2^20 buckets, this 11.1.
 constexpr int kFreeScan = 8;
 
 __global__ __launch_bounds__(256) void export_free_kernel(MapDev m, uint32_t num_buckets, int32_t* keys, float* w,

@@ -417,9 +417,12 @@ size_t flood_member_bytes(const FrameDev& f) {
 }
 
 // Frames of more tiles than this (8 rounds of the drain's 16 wavefronts) get a
-// parallel pass over the marked tiles before the drain.  640x480 (80 tiles),
-// without / with: 46.8 / 48.4 us with nothing to fill, 65.1 / 67.3 with a
-// tenth of the view moving; 1280x720 (240 tiles), a third moving: 92.8 / 84.1.
+// parallel pass over the marked tiles before the drain.  With nothing to fill it
+// costs 1 to 3 us.  Masks of frames with a third and two thirds of the view
+// moving, means of three scenes, without / with: 640x480 (80 tiles) 47 / 48 and
+// 51 / 51 us, 848x480 (112) 48 / 49 and 50 / 49, 960x540 (135) 50 / 49 and
+// 55 / 51, 1024x640 (160) 57 / 56 and 59 / 55, 1280x720 (240) 60 / 56 and
+// 65 / 60.
 constexpr int kPassTiles = 128;
 
 void launch_mask(Batch& b, int df, int st, const rf_mask_params& mp, void* edges, hipStream_t s) {

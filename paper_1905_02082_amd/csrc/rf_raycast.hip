@@ -14,7 +14,7 @@
 // trip to the map), and nearly all of them lie in free space, where every
 // sample is defined and positive.  Two ways round that chain, both with the
 // decisions of sampling one by one:
-//   few rays (holes of a frame): 16 lanes share a ray, each with a sample of
+//   few rays (holes of a frame): 32 lanes share a ray, each with a sample of
 //     its own, and the first crossing of a batch is found by a ballot;
 //   many rays: the blocks the tile's rays pass are looked up and tested once
 //     per tile by whole wavefronts, and the samples in blocks known to hold

@@ -390,7 +390,10 @@ constexpr int kMaxProbe = 8;   // a key is placed within 8 slots of its home or 
 // coarsest levels (64 pixels of a 640-pixel row and more) is up to 11 blocks wide at
 // 0.5 cm; with 8 most of its lookups went on to the LDS hash and the table:
 // with 16 a 640x480 step takes 965 us instead of 996 at 0.5 cm, 746 instead of
-// 775 at 1 cm.  The finer levels' tiles fit 8, which clears faster.
+// 775 at 1 cm.  The finer levels' tiles fit 8, which clears faster.  Coarse
+// voxels would fit 8 too, for little: a registration of 640x480 over four levels
+// takes 344 us with 8 and 348 with 16 at 2 cm (160x120 285 both, 320x240 294 and
+// 297), 355 both at 1.4 cm, but 481 and 398 at 1 cm, 534 and 455 at 0.6 cm.
 __host__ __device__ constexpr int win_of(int slots) { return slots >= 512 ? 16 : 8; }
 constexpr int kFarOrigin = 0x40000000;  // window origin that no block coordinate reaches
 
@@ -1018,9 +1021,10 @@ __global__ __launch_bounds__(kTrackBlock) void residual_kernel(Batch b, float ga
     xform(R, t, x, y);
     float S, Iv, g3[3], h3[3];
     int mark;  // nothing is written back
-    // a tile without pairs (a map that has not tracked at this level) has nothing
-    // to gain from filling a cache that is not kept: 640x480 18.0 us through it,
-    // 12.9 without; 1280x720 31 and 22.8; with its pairs 8.8
+    // a tile without pairs (a map that has not tracked at this level; never in a
+    // frame, whose mask follows a registration) has nothing to gain from filling
+    // a cache that is not kept: 640x480 18.0 us through it, 12.9 without;
+    // 1280x720 31 and 22.8; with its pairs 8.8
     const bool defined = s_cache.cnt != 0 ? sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3,
                                                                             CachedSlots<SLOTS>{cache, &mark})
                                           : sample_map<STORAGE, false, false>(m, y, S, g3, Iv, h3);
